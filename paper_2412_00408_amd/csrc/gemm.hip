@@ -3,28 +3,45 @@
 // input and weight), binary32 accumulation on the matrix cores, the GELU of
 // Eq. 7 with QuAKE / QuAKE2 / EXACT applied to the binary32 accumulators in
 // the epilogue, output in the input format. This is QuAKE inside a fused consumer: the GELU
-// costs no HBM traffic of its own, and its VALU work runs beside the MFMAs.
+// costs no HBM traffic of its own.
 //
-// Tiling: a workgroup (4 waves) computes a 128 x BN tile of y (BN = 192 when
-// n is a multiple of 192 and those tiles cover every CU, else 128), each wave
-// a 64 x BN/2 quarter as 2 x BN/64 blocks of v_mfma_f32_32x32x16_bf16. The
-// wider tile reads 17 % fewer
-// LDS bytes per matrix-core operation (each A fragment feeds three blocks
-// instead of two), which is what bounds this loop. K advances in slabs of 64:
-// the next slab is loaded from HBM into registers while the current one is
-// multiplied out of LDS (rows padded by 16 bytes so the 16-byte fragment reads
-// of 8 consecutive rows hit distinct banks). With two workgroups per CU the
-// other workgroup's products cover a slab's load latency; a grid of at most
-// one tile per CU over a long k (>= 1024) has nothing to cover it, and there
-// each slab is loaded two slabs ahead into a second register set.
-// Operand lane layout of the 32x32x16 bf16 MFMA (checked on the device):
-// lane l holds row (l mod 32) and k = 8 (l / 32) .. +7 of A, and column
-// (l mod 32), the same k, of B; accumulator r of lane l is row
-// 8 (r / 4) + 4 (l / 32) + (r mod 4), column l mod 32.
+// What bounds it, and what follows from that (MI355X, random operands):
+//  * Power. With random operands the matrix cores pull the clock down to
+//    1.6-2.0 GHz, and v_mfma_*_16x16x32 does the same products for less energy
+//    than 32x32x16: 1973 against 1584 TFLOP/s in a loop of nothing else. So the
+//    blocks are 16 x 16.
+//  * Operand delivery. A CU takes 64 bytes per clock from L2, and L2 serves
+//    whole 128-byte lines (rows of 64 bytes got half that rate with every CU
+//    loading: 30 against 59 bytes per clock and CU), so K advances in slabs of
+//    64 elements = one line per row, and the tiles are as wide as registers
+//    and LDS allow: 256 x 256 and 256 x 192 need 1/2 and 7/12 of that rate at
+//    the full matrix-core rate.
+//  * Issue. Slabs go from L2 to LDS directly (global_load_lds, no registers, no
+//    ds_write). A burst of those loads stalls every wave that issues it, so
+//    they and the fragment reads are placed one by one between the products
+//    (4096 x 4096 x 4096 with 256 x 256 tiles of 32 x 32 blocks: 125 us with
+//    bursts, 109 us with the loads spread out; 100 us with 16 x 16 blocks).
+//  * Latency. The x and w tiles have SA and SB stages in LDS (up to 160 KB), so
+//    that a slab is loaded one to four slabs ahead; one barrier per slab.
+//  * The output. Tiles end together, so the write is not hidden; it leaves
+//    through LDS as whole rows, 16 bytes per lane, and non-temporally, so that
+//    L2 has little left to write back at the end of the kernel (the product of
+//    16384 x 4096 x 1024: 126.8 -> 112.1 us).
+// Measured against the kernel this replaced (128-wide tiles of 32 x 32 blocks,
+// slabs through registers; back to back, with the GELU): bf16 4096 x 3072 x 768
+// 26.5 -> 21.9 us, 4096 x 768 x 3072 (no GELU) 37.2 -> 22.3 us, binary16
+// 16384 x 4096 x 1024 (EXACT) 187.0 -> 129.0 us (1065 TFLOP/s).
+//
+// Operand lane layout of the 16x16x32 16-bit MFMA: lane l holds row l mod 16
+// and k = 8 (l / 16) .. +7 of A, column l mod 16 and the same k of B;
+// accumulator r of lane l is row 4 (l / 16) + r, column l mod 16. The w
+// fragment is passed as A, so that a lane's four accumulators are four
+// consecutive columns of one row of y.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "quake_device.hpp"
 #include "quake_host.hpp"
@@ -33,30 +50,21 @@ namespace qk {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// one 32x32x16 matrix-core step on raw 16-bit operands of format DT
+// one 16x16x32 matrix-core step on raw 16-bit operands of format DT
 template <int DT>
-__device__ __forceinline__ f32x16_t mfma16(u32x4 a, u32x4 b, f32x16_t c) {
+__device__ __forceinline__ f32x4_t mfma16(u32x4 a, u32x4 b, f32x4_t c) {
   if constexpr (DT == BF16)
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
   else
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a),
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a),
                                                   __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
-template <int DT>
-__device__ __forceinline__ uint16_t narrow16(float v) {
-  if constexpr (DT == BF16)
-    return __builtin_bit_cast(uint16_t, (__bf16)v);
-  else
-    return __builtin_bit_cast(uint16_t, (_Float16)v);
-}
 
-constexpr int kBM = 128, kBK = 64;
-constexpr int kLdsRow = kBK + 8;   // bf16 elements per LDS row (144 bytes)
-constexpr int kGemmThreads = 256;
-constexpr int kMaxBN = 192;
+constexpr int kBK = 64;          // elements of k per slab: one 128-byte line per row
+constexpr int kSlabRow = 128;    // bytes of an LDS row
 
 struct GemmArgs {
   const uint16_t* x;
@@ -66,203 +74,337 @@ struct GemmArgs {
   int64_t ldx, ldw, ldy;   // elements
   float c0, c1, a;         // GELU constants (Eq. 7 folded into Eq. 5)
   uint32_t tiles_m, tiles_n;
-  uint32_t xcd_split;      // tiles_m % 4 == 0 and tiles_n % 2 == 0
+  int32_t op;              // quake_mode of the GELU, or -1 for the product alone
+  uint32_t vec;            // rows of y are 16-byte aligned
 };
 
-// OCC: workgroups per CU the register budget is set for (3 at BN = 128: at
-// most 168 VGPRs; 2 at BN = 192 and with two register sets). AHEAD: slabs
-// in flight (1: the next slab, one register set; 2: two register sets).
-template <int DT, int MODE, bool GELU, int BN, int OCC, int AHEAD>
-__global__ __launch_bounds__(kGemmThreads, OCC) void gemm_kernel(GemmArgs g) {
-  constexpr int TN = BN / 64;                     // 32 x 32 blocks per wave along n
-  constexpr int VA = kBM * 8 / kGemmThreads;      // 16-byte vectors per thread per slab
-  constexpr int VB = BN * 8 / kGemmThreads;
-  static_assert(BN % 64 == 0 && BN <= kMaxBN && BN * 8 % kGemmThreads == 0, "tile width");
-  __shared__ __attribute__((aligned(16))) uint16_t sx[kBM * kLdsRow];
-  __shared__ __attribute__((aligned(16))) uint16_t sw[BN * kLdsRow];
-  const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  // Workgroups go to the 8 XCDs round-robin (blockIdx mod 8). When the tile
-  // grid splits into 4 x 2 equal blocks, XCD j gets block (j / 2, j mod 2),
-  // so the rows of x and w its tiles share stay in its own L2.
-  int tm, tn;
-  if (g.xcd_split) {
-    const uint32_t xcd = blockIdx.x & 7u, local = blockIdx.x >> 3;
-    const uint32_t bm = g.tiles_m >> 2, bn = g.tiles_n >> 1;
-    tm = (int)((xcd >> 1) * bm + local / bn);
-    tn = (int)((xcd & 1u) * bn + local % bn);
-  } else {
-    tm = (int)(blockIdx.x / g.tiles_n);
-    tn = (int)(blockIdx.x % g.tiles_n);
-  }
-  const int row0 = tm * kBM, col0 = tn * BN;
+// where lanes past the end of k load from
+__device__ const u32x4 g_zero16 = {0u, 0u, 0u, 0u};
 
-  // Slab loads: 8 16-byte vectors per row of each operand; thread t takes
-  // vectors t + 256 i, i.e. row v / 8 and k-vector v mod 8. Rows past m (n)
-  // re-read the last row; k past the end re-reads k-vector 0 and is replaced
-  // by zeros when the slab is written to LDS (k is a multiple of 8). Nothing
-  // consumes the loaded registers before that write, so the loads stay in
-  // flight during the previous slab's MFMAs.
-  u32x4 rxs[2][VA], rws[2][VB];
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  auto load_slab = [&](u32x4 (&rx)[VA], u32x4 (&rw)[VB], int k0) {
-#pragma unroll
-    for (int i = 0; i < VA; ++i) {
-      const int v = t + kGemmThreads * i;
-      const int r = v >> 3, kk = k0 + 8 * (v & 7);
-      const int gm = min(row0 + r, g.m - 1);
-      const int kc = kk < g.k ? kk : 0;
-      rx[i] = *reinterpret_cast<const u32x4*>(g.x + (int64_t)gm * g.ldx + kc);
-    }
-#pragma unroll
-    for (int i = 0; i < VB; ++i) {
-      const int v = t + kGemmThreads * i;
-      const int r = v >> 3, kk = k0 + 8 * (v & 7);
-      const int gn = min(col0 + r, g.n - 1);
-      const int kc = kk < g.k ? kk : 0;
-      rw[i] = *reinterpret_cast<const u32x4*>(g.w + (int64_t)gn * g.ldw + kc);
-    }
-  };
-  auto store_slab = [&](const u32x4 (&rx)[VA], const u32x4 (&rw)[VB], int k0) {
-#pragma unroll
-    for (int i = 0; i < VA; ++i) {
-      const int v = t + kGemmThreads * i;
-      const int r = v >> 3, c = 8 * (v & 7);
-      *reinterpret_cast<u32x4*>(sx + r * kLdsRow + c) = (k0 + c < g.k) ? rx[i] : zero;
-    }
-#pragma unroll
-    for (int i = 0; i < VB; ++i) {
-      const int v = t + kGemmThreads * i;
-      const int r = v >> 3, c = 8 * (v & 7);
-      *reinterpret_cast<u32x4*>(sw + r * kLdsRow + c) = (k0 + c < g.k) ? rw[i] : zero;
-    }
-  };
-
-  f32x16_t acc[2][TN];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-  const int nk = (g.k + kBK - 1) / kBK;
-  // AHEAD = 2: two register sets, each slab's loads issued two slabs ahead.
-  // Those loads are unconditional (past the end of k they re-read k-vector 0,
-  // and nothing stores them), so the compiler's wait counts stay exact:
-  // storing a slab waits only for its own set, the other set's loads stay in
-  // flight.
-  load_slab(rxs[0], rws[0], 0);
-  __builtin_amdgcn_sched_barrier(0);   // set 0's loads all before set 1's
-  if constexpr (AHEAD == 2) load_slab(rxs[1], rws[1], kBK);
-  __builtin_amdgcn_sched_barrier(0);
-  const int fr = lane & 31, fk = 8 * (lane >> 5);
-  auto slab = [&](int kt, u32x4 (&rx)[VA], u32x4 (&rw)[VB]) {
-    __syncthreads();   // every wave is done reading the previous slab
-    store_slab(rx, rw, kt * kBK);
-    __syncthreads();
-    if constexpr (AHEAD == 2) load_slab(rx, rw, (kt + 2) * kBK);   // in flight for two slabs
-    else if (kt + 1 < nk) load_slab(rxs[0], rws[0], (kt + 1) * kBK);   // one set: the next slab
-#pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-      u32x4 af[2], bf[TN];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        af[i] = *reinterpret_cast<const u32x4*>(sx + (wm * 64 + 32 * i + fr) * kLdsRow + ks * 16 + fk);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bf[j] = *reinterpret_cast<const u32x4*>(sw + (wn * 32 * TN + 32 * j + fr) * kLdsRow + ks * 16 + fk);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = mfma16<DT>(af[i], bf[j], acc[i][j]);
-    }
-  };
-  // every way back to the loop head has issued both sets in the same order
-  // (an exit taken before the second set would make the waits conservative)
-  if constexpr (AHEAD == 2) {
-    for (int kt = 0;; kt += 2) {
-      slab(kt, rxs[0], rws[0]);
-      if (kt + 1 >= nk) break;
-      slab(kt + 1, rxs[1], rws[1]);
-      if (kt + 2 >= nk) break;
-    }
-  } else {
-    for (int kt = 0; kt < nk; ++kt) slab(kt, rxs[0], rws[0]);
-  }
-
-  // Epilogue: GELU on the binary32 accumulators, round to the 16-bit format,
-  // store. Accumulator r of block (i, j) in lane l is row
-  // 32 i + 8 (r / 4) + 4 (l / 32) + r mod 4 of the wave's rows and column
-  // 32 j + l mod 32 of its columns: for each (i, r) a half-wave stores 64
-  // contiguous bytes of one row. In a tile inside m and n (uniform) the row
-  // base of each (i, r) is uniform and the lane adds a 32-bit offset, so the
-  // stores need no per-element address arithmetic or bounds checks.
-  // the wave index made uniform here keeps the row bases of the stores in
-  // scalar registers (the main loop above is faster with its LDS fragment
-  // addresses formed per lane)
-  const int wu = __builtin_amdgcn_readfirstlane(wave);
-  const int wrow = row0 + (wu >> 1) * 64, wcol = col0 + (wu & 1) * 32 * TN;
-  if (row0 + kBM <= g.m && col0 + BN <= g.n && (int64_t)4 * g.ldy < INT32_MAX) {
-    const uint32_t lo = (uint32_t)(4 * (lane >> 5)) * (uint32_t)g.ldy + (uint32_t)fr;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        uint16_t* yr = g.y + (int64_t)(wrow + 32 * i + 8 * (r >> 2) + (r & 3)) * g.ldy + wcol;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          float v = acc[i][j][r];
-          if constexpr (GELU) v = gelu_q<MODE>(v, g.c0, g.c1, g.a);
-          yr[lo + 32 * j] = narrow16<DT>(v);
-        }
-      }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = wcol + 32 * j + fr;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wrow + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        float v = acc[i][j][r];
-        if constexpr (GELU) v = gelu_q<MODE>(v, g.c0, g.c1, g.a);
-        if (row < g.m && col < g.n)
-          g.y[(int64_t)row * g.ldy + col] = narrow16<DT>(v);
-      }
-    }
+// 16 bytes per lane from each lane's p to LDS bytes lds + 16 * lane (lds
+// uniform). The asm has no register result: the data is in LDS once vmcnt says
+// so. (Issued through the builtin, every later LDS read would wait for every
+// such load, as the compiler does not tell the stages apart.)
+__device__ __forceinline__ void lds_load16(uint32_t lds, const char* p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(lds), "v"(p)
+               : "memory", "m0");
+}
+// at most N vector memory operations of this wave still in flight
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// the workgroup's barrier, no LDS access of this wave outstanding or moved across
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-template <int DT, int MODE, int BN, int OCC, int AHEAD>
-void launch_gemm(int gelu, dim3 grid, hipStream_t s, const GemmArgs& g) {
-  if (gelu)
-    hipLaunchKernelGGL((gemm_kernel<DT, MODE, true, BN, OCC, AHEAD>), grid, dim3(kGemmThreads), 0, s, g);
-  else
-    hipLaunchKernelGGL((gemm_kernel<DT, MODE, false, BN, OCC, AHEAD>), grid, dim3(kGemmThreads), 0, s, g);
+// The GELU of four accumulators (op uniform: its branches are scalar), as two
+// packed pairs.
+template <int DT>
+__device__ __forceinline__ uint2 gelu4(f32x4_t v, const GemmArgs& g, int op) {
+  float f[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (op == EXACT) f[i] = gelu_q<EXACT>(f[i], g.c0, g.c1, g.a);
+    else if (op == Q1) f[i] = gelu_q<Q1>(f[i], g.c0, g.c1, g.a);
+    else if (op == Q2) f[i] = gelu_q<Q2>(f[i], g.c0, g.c1, g.a);
+    else if (op == Q2M) f[i] = gelu_q<Q2M>(f[i], g.c0, g.c1, g.a);
+  }
+  uint2 o;
+  o.x = DT == BF16 ? pack_bf16(f[0], f[1]) : pack_f16(f[0], f[1]);
+  o.y = DT == BF16 ? pack_bf16(f[2], f[3]) : pack_f16(f[2], f[3]);
+  return o;
+}
+
+// WM x WN waves over a BM x BN tile, SA / SB stages of its x / w slab
+// (|SA - SB| <= 1); registers for two waves per SIMD.
+template <int DT, int BM, int BN, int WM, int WN, int SA, int SB>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
+  constexpr int NW = WM * WN;
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;         // 16 x 16 blocks per wave
+  constexpr int IA = BM / 8 / NW, IB = BN / 8 / NW;           // loads per wave and slab
+  constexpr int NV = IA + IB;
+  constexpr uint32_t kA = BM * kSlabRow, kB = BN * kSlabRow;  // bytes of a stage
+  constexpr uint32_t kB0 = SA * kA;                           // first w stage
+  constexpr int P = TN * 32 + 16;                             // row pitch of the epilogue's staging
+  constexpr int kLds = SA * BM * kSlabRow + SB * BN * kSlabRow;
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && NW % 2 == 0, "whole loads per wave");
+  static_assert(BM % (32 * WM) == 0 && BN % (16 * WN) == 0, "whole blocks per wave");
+  static_assert(SA >= 2 && SB >= 2 && SA - SB <= 1 && SB - SA <= 1, "stages");
+  static_assert(NW * 64 * P <= kLds && kLds <= 163840, "LDS");
+  __shared__ __attribute__((aligned(16))) char smem[kLds];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  // Tile order: workgroups go to the 8 XCDs round-robin (blockIdx mod 8); XCD j
+  // takes the j-th eighth of the tiles, in groups of 4 tile rows walked along
+  // n, so that the rows of x and w in use at a time stay in its L2.
+  const uint32_t tiles = g.tiles_m * g.tiles_n, xcd = blockIdx.x & 7u;
+  const uint32_t id = xcd * (tiles >> 3) + min(xcd, tiles & 7u) + (blockIdx.x >> 3);
+  const uint32_t gsz = 4u * g.tiles_n, first = id / gsz * 4u, in = id % gsz;
+  const uint32_t rows = min(4u, g.tiles_m - first);
+  const int row0 = (int)(first + in % rows) * BM, col0 = (int)(in / rows) * BN;
+
+  // Slab loads: one instruction fills 8 LDS rows of 128 bytes, lane l slot
+  // l mod 8 (16 bytes) of row l / 8. Slot s of row r holds k-vector s ^ (r / 2
+  // mod 8) of the row, which makes the fragment reads below free of bank
+  // conflicts. Rows past m (n) re-read the last row (never stored); k-vectors
+  // past the end of k load zeros.
+  const int kv = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
+  const char* pa[IA];
+  const char* pb[IB];
+#pragma unroll
+  for (int i = 0; i < IA; ++i)
+    pa[i] = reinterpret_cast<const char*>(
+        g.x + (int64_t)min(row0 + 8 * (wave + NW * i) + (lane >> 3), g.m - 1) * g.ldx + 8 * kv);
+#pragma unroll
+  for (int i = 0; i < IB; ++i)
+    pb[i] = reinterpret_cast<const char*>(
+        g.w + (int64_t)min(col0 + 8 * (wave + NW * i) + (lane >> 3), g.n - 1) * g.ldw + 8 * kv);
+  const int nk = (g.k + kBK - 1) / kBK;
+  // before slab kt is loaded: lanes past the end of k to the zeros
+  auto clip = [&](uint32_t kt, auto& p) {
+    if (kBK * kt + kBK > (uint32_t)g.k) {
+      const bool in_k = kBK * kt + 8 * kv < (uint32_t)g.k;
+#pragma unroll
+      for (auto& q : p) q = in_k ? q : reinterpret_cast<const char*>(&g_zero16);
+    }
+  };
+  auto load_a = [&](uint32_t stage, int i) {
+    lds_load16(lds0 + stage * kA + 1024 * (wave + NW * i), pa[i]);
+    pa[i] += 2 * kBK;
+  };
+  auto load_b = [&](uint32_t stage, int i) {
+    lds_load16(lds0 + kB0 + stage * kB + 1024 * (wave + NW * i), pb[i]);
+    pb[i] += 2 * kBK;
+  };
+  // Loads are waited for in the order of issue, so of each slab the operand
+  // with fewer stages, which is needed sooner, goes first.
+  constexpr bool kAFirst = SA < SB;
+  uint32_t fa = 0, fb = 0;   // the stages being refilled
+  auto load = [&](int d) {   // d-th of the NV loads of a refill
+    if (kAFirst) {
+      if (d < IA) load_a(fa, d); else load_b(fb, d - IA);
+    } else {
+      if (d < IB) load_b(fb, d); else load_a(fa, d - IB);
+    }
+  };
+
+  // Fragment reads: k-step ks (32 elements) of a slab, k-vector 4 ks + lane / 16
+  // of row lane mod 16 of a block.
+  const int fr = lane & 15, h = lane >> 4;
+  const uint32_t kv0 = 16 * (h ^ (fr >> 1)), kv1 = 16 * ((4 + h) ^ (fr >> 1));
+  const uint32_t oa = (wm * TM * 16 + fr) * kSlabRow, ob = kB0 + (wn * TN * 16 + fr) * kSlabRow;
+  u32x4 af[TM], bf[2][TN];
+  auto read_a = [&](uint32_t stage, int ks, int i) {
+    af[i] = *reinterpret_cast<const u32x4*>(smem + (oa + stage * kA + (ks ? kv1 : kv0)) + 2048 * i);
+  };
+  auto read_b = [&](uint32_t stage, int ks, int j) {
+    bf[ks][j] = *reinterpret_cast<const u32x4*>(smem + (ob + stage * kB + (ks ? kv1 : kv0)) + 2048 * j);
+  };
+
+  f32x4_t acc[TM][TN] = {};
+  // the first SA / SB slabs, in the order their refills would have had
+#pragma unroll
+  for (int j = 0; j < (SA > SB ? SA : SB); ++j) {
+    auto first_a = [&] {
+      if (j < SA) {
+        clip(j, pa);
+#pragma unroll
+        for (int i = 0; i < IA; ++i) load_a(j, i);
+      }
+    };
+    if (kAFirst) first_a();
+    if (j < SB) {
+      clip(j, pb);
+#pragma unroll
+      for (int i = 0; i < IB; ++i) load_b(j, i);
+    }
+    if (!kAFirst) first_a();
+  }
+  wait_loads<(SA - 1) * IA + (SB - 1) * IB>();   // slab 0 is there
+  lds_barrier();
+  uint32_t ca = 0, cb = 0;   // the current slab's stages
+#pragma unroll
+  for (int i = 0; i < TM; ++i) read_a(0, 0, i);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) read_b(0, 0, j);
+
+  // One slab: TM TN products of its k-step 0, then of its k-step 1, row of
+  // blocks by row of blocks. After the last product of a row the row's x
+  // fragment is read again for the next k-step, in place; the w fragments have
+  // two sets. The barrier stands after R1 rows of k-step 1: every wave's reads
+  // of the slab are done there, the next slab has landed, and the slab's
+  // stages are refilled from there until k-step 1 of the next slab.
+  constexpr int M = TM * TN, R1 = TM >= 4 ? 2 : 1, Q1st = R1 * TN;
+  constexpr int kWait = (SA - 2) * IA + (SB - 2) * IB;   // loads that may still be in flight there
+  constexpr int E = SA > SB ? IB : SA < SB ? IA : (NV + 1) / 2;   // loads of a refill beside k-step 1
+  auto slab = [&](auto refill, int kt) {
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+      const int i = q / TN, j = q % TN;
+      acc[i][j] = mfma16<DT>(bf[0][j], af[i], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (j == TN - 1) read_a(ca, 1, i);
+      if (q < TN) read_b(cb, 1, q);
+      if (decltype(refill)::value) {
+#pragma unroll
+        for (int d = E; d < NV; ++d)
+          if ((2 * (d - E) + 1) * M / (2 * (NV - E)) == q) load(d);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+      const int i = q / TN, j = q % TN;
+      acc[i][j] = mfma16<DT>(bf[1][j], af[i], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+      const int p = q - (Q1st - 1);
+      if (p == 0) {
+        wait_loads<kWait>();
+        lds_barrier();
+        fa = ca;
+        fb = cb;
+        clip(kt + SA, pa);
+        clip(kt + SB, pb);
+        ca = ca + 1 == SA ? 0 : ca + 1;
+        cb = cb + 1 == SB ? 0 : cb + 1;
+      }
+      if (p >= 0) {   // past the last slab: zeros, or what the stage last held; never used
+        if (p < R1) read_a(ca, 0, p);
+        else if (j == TN - 1) read_a(ca, 0, i);
+        if (p < TN) read_b(cb, 0, p);
+#pragma unroll
+        for (int d = 0; d < E; ++d)
+          if ((2 * d + 1) * (M - Q1st) / (2 * E) == p) load(d);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  slab(std::false_type{}, 0);   // the prologue filled every stage
+  for (int kt = 1; kt < nk; ++kt) slab(std::true_type{}, kt);
+  wait_loads<0>();   // no load into LDS outlives its stage
+
+  // Epilogue: GELU on the binary32 accumulators, rounded to the 16-bit format,
+  // two rows of blocks (32 rows of y) at a time through this wave's own LDS
+  // (two halves in turn) to whole rows. Accumulator r of block (i, j) in lane l
+  // is row 16 i + l mod 16, column 16 j + 4 (l / 16) + r of the wave's part.
+  __syncthreads();
+  constexpr int CH = TN * 2;   // 16-byte vectors per row
+  const int wrow = row0 + wm * TM * 16, wcol = col0 + wn * TN * 16;
+  auto epilogue = [&](auto op) {
+#pragma unroll
+    for (int i = 0; i < TM; i += 2) {
+      char* st = smem + (2 * wave + ((i >> 1) & 1)) * (32 * P);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          *reinterpret_cast<uint2*>(st + (16 * u + fr) * P + 32 * j + 8 * h) =
+              gelu4<DT>(acc[i + u][j], g, decltype(op)::value);
+      __builtin_amdgcn_wave_barrier();
+      if (g.vec) {
+#pragma unroll
+        for (int q = 0; q < 32 * CH / 64; ++q) {
+          const int c = q * 64 + lane, rr = c / CH, cc = c % CH;
+          const u32x4 v = *reinterpret_cast<const u32x4*>(st + rr * P + 16 * cc);
+          const uint32_t row = wrow + 16 * i + rr, col = wcol + 8 * cc;
+          if (row >= (uint32_t)g.m) continue;
+          uint16_t* yr = g.y + (int64_t)row * g.ldy + col;
+          if (col + 8 <= (uint32_t)g.n)
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(yr));
+          else
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (col + e < (uint32_t)g.n) yr[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+        }
+      } else {
+        // rows of any alignment: one element per lane, 128 bytes of a row at a time
+#pragma unroll 4
+        for (int q = 0; q < 32 * TN * 16 / 64; ++q) {
+          const int c = q * 64 + lane, rr = c / (TN * 16), cc = c % (TN * 16);
+          const uint16_t v = *reinterpret_cast<const uint16_t*>(st + rr * P + 2 * cc);
+          const uint32_t row = wrow + 16 * i + rr, col = wcol + cc;
+          if (row < (uint32_t)g.m && col < (uint32_t)g.n) g.y[(int64_t)row * g.ldy + col] = v;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  switch (g.op) {
+    case EXACT: epilogue(std::integral_constant<int, EXACT>{}); break;
+    case Q1: epilogue(std::integral_constant<int, Q1>{}); break;
+    case Q2: epilogue(std::integral_constant<int, Q2>{}); break;
+    case Q2M: epilogue(std::integral_constant<int, Q2M>{}); break;
+    default: epilogue(std::integral_constant<int, -1>{}); break;
+  }
+}
+
+template <int DT, int BM, int BN, int WM, int WN, int SA, int SB>
+void launch_tile(GemmArgs g, hipStream_t s) {
+  g.tiles_m = (uint32_t)(((int64_t)g.m + BM - 1) / BM);
+  g.tiles_n = (uint32_t)(((int64_t)g.n + BN - 1) / BN);
+  hipLaunchKernelGGL((gemm_kernel<DT, BM, BN, WM, WN, SA, SB>), dim3(g.tiles_m * g.tiles_n),
+                     dim3(64 * WM * WN), 0, s, g);
+}
+
+// The tiles, and what a launch of each takes (measured with the GELU in bf16, random
+// operands, every CU busy): `per_cu` workgroups fit a CU; a round of them takes
+// `fixed` + slab us per 64 elements of k, with `slab1` while there is no more than
+// one per CU, and every further round of tiles adds `again` + slab. Large tiles
+// need the least operand traffic, small ones fill the chip where m n is small;
+// the estimate picks between them. Over 70 random shapes (m to 16384, n to
+// 4096, k to 4096) the picks took 1.9 % longer than the best of sixteen
+// tiles measured on each.
+struct Tile {
+  int bm, bn, per_cu;
+  float fixed, again, slab1, slab;
+};
+constexpr Tile kTiles[] = {
+    {256, 256, 1, 13.0f, 8.3f, 1.30f, 1.30f},
+    {256, 192, 1, 11.0f, 6.6f, 1.01f, 1.01f},
+    {128, 128, 1, 5.9f, 4.1f, 0.44f, 0.44f},
+    {128, 64, 2, 4.2f, 2.5f, 0.32f, 0.56f},
+    {64, 64, 2, 3.7f, 1.5f, 0.19f, 0.37f},
+    {64, 32, 1, 3.6f, 2.2f, 0.155f, 0.155f},
+};
+
+inline int pick_tile(int64_t m, int64_t n, int64_t k, int cus) {
+  const double slabs = (double)((k + kBK - 1) / kBK);
+  int best = 0;
+  double best_us = 0;
+  for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+    const Tile& t = kTiles[i];
+    const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn);
+    const int64_t slots = (int64_t)t.per_cu * cus;
+    const int64_t full = tiles / slots, rest = tiles % slots;
+    const double rounds = (double)(full + (rest != 0));
+    const double us = t.fixed + (rounds - 1) * t.again + (double)full * slabs * t.slab +
+                      (rest == 0 ? 0.0 : slabs * (rest <= cus ? t.slab1 : t.slab));
+    if (i == 0 || us < best_us) {
+      best = i;
+      best_us = us;
+    }
+  }
+  return best;
 }
 
 template <int DT>
-void launch_gemm_dt(int mode, bool wide, bool ahead2, int gelu, dim3 grid, hipStream_t s,
-                    const GemmArgs& g) {
-#define QK_GEMM_CASE(M)                                      \
-  if (mode == M) {                                           \
-    if (ahead2) {                                            \
-      if (wide)                                              \
-        launch_gemm<DT, M, 192, 2, 2>(gelu, grid, s, g);     \
-      else                                                   \
-        launch_gemm<DT, M, 128, 2, 2>(gelu, grid, s, g);     \
-    } else if (wide) {                                       \
-      launch_gemm<DT, M, 192, 2, 1>(gelu, grid, s, g);       \
-    } else {                                                 \
-      launch_gemm<DT, M, 128, 3, 1>(gelu, grid, s, g);       \
-    }                                                        \
+void launch_gemm(int tile, const GemmArgs& g, hipStream_t s) {
+  switch (tile) {
+    case 0: launch_tile<DT, 256, 256, 2, 4, 3, 2>(g, s); break;
+    case 1: launch_tile<DT, 256, 192, 4, 2, 2, 3>(g, s); break;
+    case 2: launch_tile<DT, 128, 128, 4, 2, 5, 5>(g, s); break;
+    case 3: launch_tile<DT, 128, 64, 2, 2, 3, 3>(g, s); break;
+    case 4: launch_tile<DT, 64, 64, 2, 2, 4, 4>(g, s); break;
+    default: launch_tile<DT, 64, 32, 2, 2, 8, 8>(g, s); break;
   }
-  QK_GEMM_CASE(EXACT) QK_GEMM_CASE(Q1) QK_GEMM_CASE(Q2) QK_GEMM_CASE(Q2M)
-#undef QK_GEMM_CASE
 }
 
 }  // namespace qk
@@ -280,34 +422,24 @@ extern "C" quake_status quake_linear_gelu(const void* x, const void* w, void* y,
   if (k == 0 || k % 8 != 0 || x == nullptr || w == nullptr || y == nullptr) return QUAKE_EINVAL;
   if (ldx < k || ldw < k || ldy < n || ldx % 8 != 0 || ldw % 8 != 0) return QUAKE_EINVAL;
   if (!aligned16(x) || !aligned16(w)) return QUAKE_EINVAL;
-  // 32-bit row, column and k arithmetic in the kernel: the last slab loaded
-  // (two slabs ahead) starts below k + 2 kBK
-  if (m > INT32_MAX - kBM || n > INT32_MAX - kMaxBN || k > INT32_MAX - 4 * kBK) return QUAKE_EINVAL;
+  // 32-bit row, column and k arithmetic in the kernel: the largest row and
+  // column formed are those of the last tile's last block
+  if (m > INT32_MAX - 128 || n > INT32_MAX - 192 || k > INT32_MAX - 256) return QUAKE_EINVAL;
+  if (((m + 127) / 128) * ((n + 127) / 128) > INT32_MAX) return QUAKE_EINVAL;
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
-  // the 128 x 192 tile where n allows it and its grid still covers every CU;
-  // otherwise the 128 x 128 tile, whose grid is 1.5x larger (measured
-  // 1.28x faster at 4096 x 768 x 3072, where the wide grid is 128 tiles)
-  const bool wide = n % 192 == 0 && ((m + kBM - 1) / kBM) * (n / 192) >= cus;
-  const int64_t bn = wide ? 192 : 128;
-  const int64_t tiles_m = (m + kBM - 1) / kBM, tiles_n = (n + bn - 1) / bn;
-  if (tiles_m * tiles_n > INT32_MAX) return QUAKE_EINVAL;
+  const int tile = pick_tile(m, n, k, cus);
   const Affine af = gelu_affine(mode);
-  GemmArgs g{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w),
-             static_cast<uint16_t*>(y), (int32_t)m, (int32_t)n, (int32_t)k, ldx, ldw, ldy,
-             af.c0, af.c1, gelu_a(), (uint32_t)tiles_m, (uint32_t)tiles_n,
-             (uint32_t)(tiles_m % 4 == 0 && tiles_n % 2 == 0)};
-  const dim3 grid((uint32_t)(tiles_m * tiles_n));
+  const bool vec = aligned16(y) && (ldy % 8 == 0 || m == 1);
+  const GemmArgs g{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w),
+                   static_cast<uint16_t*>(y), (int32_t)m, (int32_t)n, (int32_t)k, ldx, ldw, ldy,
+                   af.c0, af.c1, gelu_a(), 0, 0, gelu ? (int32_t)mode : -1, (uint32_t)vec};
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // at most one tile per CU and a long k: slabs loaded two ahead (measured
-  // 1.1-1.3x faster there; elsewhere the co-resident workgroup hides the
-  // latency and the second set only costs registers)
-  const bool ahead2 = tiles_m * tiles_n <= cus && k >= 1024;
   if (dtype == QUAKE_BF16)
-    launch_gemm_dt<BF16>(mode, wide, ahead2, gelu, grid, s, g);
+    launch_gemm<BF16>(tile, g, s);
   else
-    launch_gemm_dt<F16>(mode, wide, ahead2, gelu, grid, s, g);
+    launch_gemm<F16>(tile, g, s);
   return launch_status();
 }

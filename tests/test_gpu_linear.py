@@ -64,8 +64,7 @@ def _run(q, m, n, k, mode, gelu, seed, pad=0, dt="bf16"):
     return host_bits(y), ref, xb, wb
 
 
-# grids below one 128 x 192 tile per CU (256 CUs) take the 128 x 128 tile,
-# whatever n; the wide tile is tested below
+# small products (the 64 x 32 and 64 x 64 tiles): whole and ragged tiles, a k tail
 @pytest.mark.parametrize("m,n,k", [(128, 128, 64), (256, 384, 768), (200, 130, 72), (1, 1, 8),
                                    (129, 257, 136), (64, 1000, 32), (200, 192, 72),
                                    (129, 576, 136), (1, 192, 8)])
@@ -79,9 +78,8 @@ def test_shapes_and_modes(q, m, n, k, mode, dt):
                "linear %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
 
 
-# a grid of at most one tile per CU over k >= 1024 loads every slab two slabs
-# ahead into a second register set: odd and even slab counts, a k tail,
-# ragged m and n, both tile widths
+# long k (more slabs than any tile has stages): odd and even slab counts, a k
+# tail, ragged m and n
 @pytest.mark.parametrize("m,n,k", [(128, 192, 1024), (200, 130, 1032), (1, 1, 2056),
                                    (129, 576, 1096), (300, 384, 4096)])
 @pytest.mark.parametrize("mode", [0, 2])
@@ -94,9 +92,8 @@ def test_long_k_two_slabs_ahead(q, m, n, k, mode, dt):
                "linear long k %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
 
 
-# n a multiple of 192 with at least one 128 x 192 tile per CU takes the wide
-# tile: a ragged last tile row and a k tail, and exactly 256 tiles over
-# k >= 1024 (the wide tile with slabs two ahead)
+# n a multiple of 192 over about 2048 rows: a ragged last tile row and a k tail,
+# and whole tiles over a longer k
 @pytest.mark.parametrize("m,n,k,mode,dt", [(2043, 3072, 72, 2, "bf16"), (2043, 3072, 72, 0, "f16"),
                                            (2048, 3072, 1032, 2, "bf16"), (2048, 3072, 1032, 3, "f16")])
 def test_wide_tile_grid(q, m, n, k, mode, dt):
@@ -105,6 +102,35 @@ def test_wide_tile_grid(q, m, n, k, mode, dt):
         g, r, xb, wb = _run(q, m, n, k, mode, gelu, 1670 + m % 7, dt=dt)
         _check(g, r, xb, wb, k, 2.0 if gelu else 1.0,
                "linear wide %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
+
+
+# every tile the dispatch has, on 256 CUs (in the order of its table), with
+# ragged last rows and columns, fewer and more slabs than the tile has stages and
+# a k tail; rows of y 16-byte aligned (n a multiple of 8) and not. The bound is
+# the module's; the oracle sees sampled rows and every column of them.
+TILE_SHAPES = [(8190, 4090, 72), (4000, 4088, 1032), (4050, 3060, 1096), (4090, 3064, 200),
+               (1000, 3000, 1000), (1030, 2050, 264), (2040, 1016, 1096), (300, 3072, 72),
+               (513, 1030, 8), (500, 512, 4096), (37, 3001, 776)]
+
+
+@pytest.mark.parametrize("m,n,k", TILE_SHAPES)
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_every_tile(q, m, n, k, dt):
+    say("linear gelu tiles", dt, m, n, k)
+    x = synth.normal((m, k), 1.0, dt, 1900 + m % 7)
+    w = synth.normal((n, k), 0.05, dt, 1910 + n % 7)
+    rows = np.unique(np.r_[0:min(m, 40), np.linspace(0, m - 1, 300).astype(int), max(0, m - 40):m])
+    xb, wb = host_bits(x)[rows].copy(), host_bits(w)
+    xg, wg = x.to("cuda:0"), w.to("cuda:0")
+    for mode, gelu in ((0, True), (1, True), (2, True), (3, True), (2, False)):
+        out = torch.full((m * n + 8,), 7.0, dtype=xg.dtype, device="cuda:0")
+        q.quake_linear_gelu(xg, wg, y=out[:m * n].view(m, n), mode=mode, gelu=gelu)
+        torch.cuda.synchronize()
+        assert (out[m * n:] == 7.0).all(), "writes past the output"
+        ref = oracle.linear_gelu(xb, wb, mode, gelu=gelu, dt=dt, threads=THREADS)
+        got = host_bits(out[:m * n].view(m, n)[torch.from_numpy(rows).to("cuda:0")])
+        _check(got, ref, xb, wb, k, 2.0 if gelu else 1.0,
+               "linear tile %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
 
 
 def test_strided_rows(q):
@@ -150,8 +176,7 @@ def test_bert_mlp_shape(q, mode, dt):
 
 def test_bert_down_projection_shape(q):
     """The down-projection of a BERT-base MLP over 4096 tokens, [4096, 3072] x
-    [768, 3072]^T, the product alone: 192 tiles of 128 x 128 (the wide tile
-    would leave half the CUs idle) over k = 3072, so the slabs go two ahead."""
+    [768, 3072]^T, the product alone: 192 tiles of 128 x 128 over k = 3072."""
     say("linear 4096x768x3072")
     g, r, xb, wb = _run(q, 4096, 768, 3072, 2, False, 1850)
     err = _check(g, r, xb, wb, 3072, 1.0, "bert down projection")
