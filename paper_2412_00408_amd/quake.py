@@ -87,9 +87,18 @@ def softmax_workspace(rows: int, cols: int, dtype=torch.float32, device="cuda:0"
     return torch.zeros(n, dtype=torch.uint8, device=device) if n else None
 
 
+# The small calls (softmax of 64 x 128, a linear layer of 37 rows) take a few
+# microseconds on the GPU, so this module's own time bounds them: an output it
+# has just made is not checked against the input, and torch's current stream is
+# read as a handle, without a Stream object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t: torch.Tensor, stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
     return int(torch.cuda.current_stream(t.device).cuda_stream)
 
 
@@ -101,7 +110,7 @@ def _check_io(x: torch.Tensor, y: torch.Tensor | None, contiguous=True) -> torch
     if contiguous and not x.is_contiguous():
         raise ValueError("input must be contiguous")
     if y is None:
-        y = torch.empty_like(x, memory_format=torch.contiguous_format)
+        return torch.empty_like(x, memory_format=torch.contiguous_format)
     if y.dtype != x.dtype or y.device != x.device or y.shape != x.shape:
         raise ValueError("output must match the input's dtype, device and shape")
     if contiguous and not y.is_contiguous():
@@ -183,8 +192,8 @@ def quake_linear_gelu(x, w, y=None, mode=QUAKE_2, gelu=True, stream=None):
         if t.stride(1) != 1:
             raise ValueError("%s must have a contiguous last dimension" % what)
     if y is None:
-        y = torch.empty((m, n), dtype=x.dtype, device=x.device)
-    if y.shape != (m, n) or y.dtype != x.dtype or y.stride(1) != 1:
+        y = x.new_empty((m, n))
+    elif y.shape != (m, n) or y.dtype != x.dtype or y.stride(1) != 1:
         raise ValueError("y must be [m, n] of x's dtype with a contiguous last dimension")
     _raise("quake_linear_gelu", lib.quake_linear_gelu(
         x.data_ptr(), w.data_ptr(), y.data_ptr(), m, n, k, x.stride(0), w.stride(0), y.stride(0),
@@ -236,16 +245,17 @@ def quake_attention(q, k, vt, o=None, mode=QUAKE_2, t=None, causal=True, stream=
     heads = q.numel() // max(seq * dim, 1)
     if tuple(vt.shape[:-2]) != tuple(q.shape[:-2]) or tuple(vt.shape[-2:]) != (dim, seq):
         raise ValueError("vt must be [..., dim, seq]")
-    ldv = _vt_row_stride(tuple(vt.shape), tuple(vt.stride()))
+    ldv = seq if vt.is_contiguous() else _vt_row_stride(tuple(vt.shape), tuple(vt.stride()))
     if o is None:
         o = torch.empty_like(q)
-    if o.shape != q.shape or o.dtype != q.dtype or not o.is_contiguous():
-        raise ValueError("o must be contiguous and shaped like q")
-    o0, o1 = _span(o)
-    for a, what in ((q, "q"), (k, "k"), (vt, "vt")):
-        a0, a1 = _span(a)
-        if o0 < a1 and a0 < o1:
-            raise ValueError("o must not overlap %s" % what)
+    else:
+        if o.shape != q.shape or o.dtype != q.dtype or not o.is_contiguous():
+            raise ValueError("o must be contiguous and shaped like q")
+        o0, o1 = _span(o)
+        for a, what in ((q, "q"), (k, "k"), (vt, "vt")):
+            a0, a1 = _span(a)
+            if o0 < a1 and a0 < o1:
+                raise ValueError("o must not overlap %s" % what)
     t = 1.0 / dim ** 0.5 if t is None else t
     _raise("quake_attention", lib.quake_attention(
         q.data_ptr(), k.data_ptr(), vt.data_ptr(), o.data_ptr(), heads, seq, dim, ldv,
@@ -266,13 +276,10 @@ def quake_softmax(x, y=None, mode=QUAKE_2, t=1.0, stream=None, workspace=None,
     workgroups that exchange their maxima and sums (quake_softmax_ws)."""
     if x.dim() == 0:
         raise ValueError("softmax needs at least one dimension")
-    _check_io(x, None, contiguous=False)
-    if y is None:
-        y = torch.empty_like(x, memory_format=torch.contiguous_format)
-    if y.dtype != x.dtype or y.device != x.device or y.shape != x.shape:
-        raise ValueError("output must match the input's dtype, device and shape")
+    made = y is None
+    y = _check_io(x, y, contiguous=False)
     rows, cols, ldx = _rows_view(x, "input")
-    _, _, ldy = _rows_view(y, "output")
+    ldy = cols if made else _rows_view(y, "output")[2]
     args = (x.data_ptr(), y.data_ptr(), rows, cols, ldx, ldy, DTYPES[x.dtype], MODES[mode], t)
     if workspace is not None:
         if _fn != "quake_softmax":
@@ -301,13 +308,10 @@ def quake_softmax_causal(x, y=None, period=None, shift=0, mode=QUAKE_2, t=1.0, w
     vector is masked, if write_masked is False)."""
     if x.dim() == 0:
         raise ValueError("softmax needs at least one dimension")
-    _check_io(x, None, contiguous=False)
-    if y is None:
-        y = torch.empty_like(x, memory_format=torch.contiguous_format)
-    if y.dtype != x.dtype or y.device != x.device or y.shape != x.shape:
-        raise ValueError("output must match the input's dtype, device and shape")
+    made = y is None
+    y = _check_io(x, y, contiguous=False)
     rows, cols, ldx = _rows_view(x, "input")
-    _, _, ldy = _rows_view(y, "output")
+    ldy = cols if made else _rows_view(y, "output")[2]
     period = cols if period is None else period
     _raise("quake_softmax_causal", lib.quake_softmax_causal(
         x.data_ptr(), y.data_ptr(), rows, cols, ldx, ldy, period, shift, int(bool(write_masked)),
