@@ -49,7 +49,14 @@ constexpr int kAttnLongMaxS = 131072;   // longest sequence (two-pass kernel)
 constexpr int kAttnQ = 32;              // queries per workgroup
 constexpr int kAttnWaves = 4;           // waves of the two-pass workgroup
 constexpr int kAttnThreads = 64 * kAttnWaves;
-// Two-pass workgroups take two groups of 32 queries from this many such
+// With 16-byte rows of V^T two-pass workgroups take two groups of 32 queries
+// (the pipelined kernel) from these values of tiles * seq on, else one group:
+// measured (us, one group -> pipelined) without the mask 1 x 1025 12.4 -> 15.6,
+// 1 x 4096 36.9 -> 36.3, 4 x 2048 22.3 -> 21.6, 8 x 2048 27.0 -> 22.0; with it
+// 8 x 2048 20.0 -> 21.5, 16 x 2048 28.5 -> 26.6, 4 x 4096 44.3 -> 37.1,
+// 16 x 4001 95.3 -> 72.7.
+constexpr int64_t kAttnPipeMin = 1 << 18, kAttnPipeMinCausal = 1 << 20;
+// Other rows take two groups of 32 queries from this many such
 // tiles on (two workgroups per CU of 256 without the mask; with it four, as
 // the longest causal tiles then take twice as long and the launch's tail
 // grows), else one group.
@@ -238,13 +245,13 @@ __device__ __forceinline__ float tree_sum(const float (&v)[TOTAL]) {
 // order, normalises them by 1 / sum and stores them, four consecutive dims
 // (8 bytes) at a time. Every wave reaches every barrier: lanes of queries past
 // s only skip their stores.
-template <int DT, int W, int QG>
-__device__ __forceinline__ void attn_finish(u32x4_t (*s_buf)[512], float* s_sum,
+template <int DT, int W, int QG, int N>
+__device__ __forceinline__ void attn_finish(u32x4_t (*s_buf)[N], float* s_sum,
                                             const f32x16_t (&oacc)[QG][2], const float (&part)[QG],
                                             const float (&m)[QG], int wave, int lane, int q0,
                                             int S, uint16_t* ohead) {
   constexpr int R = 32 / W;
-  static_assert(W == 4 || W == 8, "four or eight waves");
+  static_assert((W == 4 || W == 8) && N >= 512, "four or eight waves, 8 KB each");
   const int fr = lane & 31;
 #pragma unroll
   for (int c = 0; c < QG; ++c) {
@@ -454,7 +461,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 4 : 1) void attn_kernel(AttnArgs g
 
   const f32x16_t oacc1[1][2] = {{oacc[0], oacc[1]}};
   const float part1[1] = {part}, m1[1] = {m};
-  attn_finish<DT, W, 1>(s_buf, &s_sum[0][0], oacc1, part1, m1, wave, lane, q0, S,
+  attn_finish<DT, W, 1, 512>(s_buf, &s_sum[0][0], oacc1, part1, m1, wave, lane, q0, S,
                         g.o + (int64_t)bh * S * kAttnD);
 }
 
@@ -663,8 +670,370 @@ __global__ __launch_bounds__(kAttnThreads, QG == 1 ? 3 : 2) void attn_long_kerne
       if (kbg < nkbc[c]) pv(c);
   }
 
-  attn_finish<DT, kAttnWaves, QG>(s_buf, s_sum, oacc, part, m, wave, lane, q0, S,
+  attn_finish<DT, kAttnWaves, QG, 512>(s_buf, s_sum, oacc, part, m, wave, lane, q0, S,
                                   g.o + (int64_t)bh * S * kAttnD);
+}
+
+// Two-pass kernel, two groups of 32 queries per workgroup, software-pipelined:
+// the same arithmetic per query, in the same order, as attn_long_kernel (so the
+// same bits), with the loads, the products and the exponentials of different
+// key blocks overlapped inside each wave.
+//
+// What bounds attn_long_kernel is that a wave does its phases one after the
+// other (stage a block through registers, four dependent products, 16
+// exponentials per lane, the second product), with two waves per SIMD to cover
+// for each other: VALU issue is busy about half of the time, the matrix cores a
+// quarter. Here
+//  * blocks go from memory to the wave's own LDS slots directly
+//    (global_load_lds, no registers), one to three blocks ahead; no barrier,
+//    only this wave's vmcnt;
+//  * operand fragments are read into the registers of the block before as soon as
+//    the last product that needs those has been issued;
+//  * pass 2 works in chunks of four scores per lane: two products of other
+//    blocks (one of S = K Q^T for the next block, one of O = V^T P for the
+//    probabilities finished in the chunks before) are issued, then the 30 VALU
+//    instructions of four QuAKE2 exponentials run beside them.
+// Pass 2 then issues VALU in all but 3 % of its cycles (2400 clocks per block of two groups
+// and wave with two waves per SIMD, 276 VALU instructions each); what is left is
+// power: the clock falls to 1.6-1.8 GHz. Measured against attn_long_kernel (us,
+// QuAKE2, same bits): 32 x 2048 76.4 -> 67.1 without the mask, 47.0 -> 41.3 with
+// it, 8 x 8192 276.6 -> 238.7 and 153.1 -> 130.1, 16 x 4001 with it 92.6 -> 70.0.
+// Blocks that some group masks or skips (at most a wave's last: the two
+// diagonal blocks of a tile and the block past s are its last two) and
+// rows past the folded clamp's range take the unpipelined code after the loop.
+constexpr int kPipeSlots = 4;   // 4 KB each per wave: pass 1 four K blocks, pass 2 two of K, two of V^T
+
+// 16 bytes per lane from base + off (base uniform, off per lane) to LDS bytes
+// lds + 16 * lane (lds uniform). The asm has no register result: the data is in
+// LDS once vmcnt says so. M0 is used by nothing else here.
+__device__ __forceinline__ void lds_load16(uint32_t lds, uint32_t off, const void* base) {
+  const uint64_t b = (uint64_t)base;   // uniform already; readfirstlane says so to the compiler
+  const uint64_t sbase = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(sbase)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+template <int DT, int MODE, int VK>
+__global__ __launch_bounds__(kAttnThreads, 2) void attn_pipe_kernel(AttnArgs g) {
+  constexpr int QG = 2, W = kAttnWaves;
+  static_assert(VK != kVtScalar, "16-byte rows of V^T");
+  __shared__ float s_max[W][QG * kAttnQ];
+  __shared__ float s_sum[W * QG * kAttnQ];
+  __shared__ u32x4_t s_ring[W][kPipeSlots * 256];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int bh, qt;
+  if (g.xcd_heads) {
+    const uint32_t x = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+    bh = (int)(x * g.xcd_heads + slot % g.xcd_heads);
+    qt = g.qtiles - 1 - (int)(slot / g.xcd_heads);
+  } else {
+    bh = (int)(blockIdx.x / (uint32_t)g.qtiles);
+    qt = g.qtiles - 1 - (int)(blockIdx.x % (uint32_t)g.qtiles);
+  }
+  const int S = g.s;
+  const int q0 = qt * QG * kAttnQ;
+  const int kblocks = (S + 31) >> 5;
+  int nkbc[QG];
+#pragma unroll
+  for (int c = 0; c < QG; ++c) nkbc[c] = g.causal ? min(kblocks, QG * qt + c + 1) : kblocks;
+  const int nkb = nkbc[QG - 1];
+  const int nlive = max(0, (nkb - wave + W - 1) / W);
+  // key blocks below this need no mask and are needed by every group; of this
+  // wave's blocks the first np
+  int plain_end = nkbc[0];
+  if (g.causal) plain_end = min(plain_end, QG * qt);
+  if (VK != kVtFull) plain_end = min(plain_end, S >> 5);
+  const int np = max(0, (plain_end - wave + W - 1) / W);
+  const int fr = lane & 31, fk = 8 * (lane >> 5), h = lane >> 5;
+  const uint16_t* Q = g.q + (int64_t)bh * S * kAttnD;
+  const uint16_t* K = g.k + (int64_t)bh * S * kAttnD;
+  const uint16_t* Vt = g.vt + (int64_t)bh * kAttnD * g.ldv;
+  u32x4_t* ring = s_ring[wave];
+  const uint32_t lds0 =
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4_t*)s_ring + wave * (kPipeSlots * 4096);
+
+  u32x4_t qf[QG][4];
+#pragma unroll
+  for (int c = 0; c < QG; ++c) {
+    const uint16_t* qr = Q + (int64_t)min(q0 + 32 * c + fr, S - 1) * kAttnD + fk;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) qf[c][ks] = ld16(qr + 16 * ks);
+  }
+  // The loads of a K (V^T) block into a slot: the slot maps of kblock_store and
+  // vblock_store, inverted (lane l of load j fills 16-byte slot 64 j + l).
+  const uint32_t koff = 128 * (lane >> 3) + 16 * ((lane & 7) ^ (lane >> 3));
+  const uint32_t voff = 2u * (uint32_t)(lane >> 2) * (uint32_t)g.ldv +
+                        16u * ((lane & 3) ^ vswz(lane >> 2));
+  auto load_k = [&](int i, int slot) {
+    const char* base = reinterpret_cast<const char*>(K + (int64_t)(W * i + wave) * 32 * kAttnD);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      lds_load16(lds0 + 4096 * slot + 1024 * j, koff ^ (16 * (j & 1)), base + 1024 * j);
+  };
+  auto load_v = [&](int i, int slot) {
+    const char* base = reinterpret_cast<const char*>(Vt + (W * i + wave) * 32);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      lds_load16(lds0 + 4096 * slot + 1024 * j, voff, base + (int64_t)32 * g.ldv * j);
+  };
+  auto read_k = [&](int slot, int ks) { return ring[256 * slot + 8 * fr + ((2 * ks + h) ^ kswz(fr))]; };
+  auto read_v = [&](int slot, int ks, int db) {
+    const int d = 32 * db + fr;
+    return ring[256 * slot + 4 * d + ((2 * ks + h) ^ vswz(d))];
+  };
+  const f32x16_t zero = {};
+
+  // ---- pass 1: the row max over the plain blocks. K block i is multiplied
+  // while the max of block i - 1 is taken and block i + 1's operands are read.
+  float m[QG];
+#pragma unroll
+  for (int c = 0; c < QG; ++c) m[c] = -INFINITY;
+  if (np > 0) {
+    u32x4_t ka[4];
+    f32x16_t sa[QG], sb[QG];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) load_k(min(i, np - 1), i);
+    wait_loads<8>();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) ka[ks] = read_k(0, ks);
+    auto step = [&](int i, f32x16_t (&cur)[QG], const f32x16_t (&prev)[QG], bool any) {
+      wait_loads<4>();   // block i + 1
+      wait_lds();        // block i - 1's slot and block i's operands have been read
+      load_k(min(i + 3, np - 1), (i + 3) & 3);
+      const int nslot = (i + 1) & 3;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+        for (int c = 0; c < QG; ++c) cur[c] = mma<DT>(ka[ks], qf[c][ks], ks == 0 ? zero : cur[c]);
+        ka[ks] = read_k(nslot, ks);
+        if (any) {
+#pragma unroll
+          for (int c = 0; c < QG; ++c)
+#pragma unroll
+            for (int r = 4 * ks; r < 4 * ks + 4; ++r) m[c] = fmaxf(m[c], prev[c][r]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    step(0, sa, sb, false);
+    int i = 1;
+    for (; i + 1 < np; i += 2) {
+      step(i, sb, sa, true);
+      step(i + 1, sa, sb, true);
+    }
+    if (i < np) {
+      step(i, sb, sa, true);
+#pragma unroll
+      for (int c = 0; c < QG; ++c) sa[c] = sb[c];
+    }
+#pragma unroll
+    for (int c = 0; c < QG; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m[c] = fmaxf(m[c], sa[c][r]);
+    wait_loads<0>();
+    wait_lds();
+  }
+  // the remaining block, if any: masks, and only the groups that need it
+  auto stage_k = [&](int kbg, u32x4_t (&ka)[4]) {
+    u32x4_t gk[4];
+    kblock_load(K, 32 * kbg, S, lane, kblock_lane_offset(lane), gk);
+    __builtin_amdgcn_wave_barrier();
+    kblock_store(ring, lane, gk);
+    __builtin_amdgcn_wave_barrier();
+    kblock_read(ring, fr, h, ka);
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto scores = [&](const u32x4_t (&ka)[4], int c, int kbg) {
+    f32x16_t sacc = mma<DT>(ka[0], qf[c][0], zero);
+#pragma unroll
+    for (int ks = 1; ks < 4; ++ks) sacc = mma<DT>(ka[ks], qf[c][ks], sacc);
+    const bool diag = g.causal && kbg == QG * qt + c;
+    if (diag || (VK != kVtFull && 32 * kbg + 32 > S)) {
+      const int query = q0 + 32 * c + fr;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = 32 * kbg + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (key >= S || (diag && key > query)) sacc[r] = -INFINITY;
+      }
+    }
+    return sacc;
+  };
+  for (int i = np; i < nlive; ++i) {
+    const int kbg = W * i + wave;
+    u32x4_t ka[4];
+    stage_k(kbg, ka);
+#pragma unroll
+    for (int c = 0; c < QG; ++c)
+      if (kbg < nkbc[c]) {
+        const f32x16_t sacc = scores(ka, c, kbg);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) m[c] = fmaxf(m[c], sacc[r]);
+      }
+  }
+  wait_lds();   // before the slots are loaded again
+  // pass 2's slots: K block i in slot i mod 2, V^T block i in slot 2 + i mod 2
+  if (np > 0) {
+    load_k(0, 0);
+    load_k(min(1, np - 1), 1);
+    load_v(0, 2);
+  }
+#pragma unroll
+  for (int c = 0; c < QG; ++c) {
+    m[c] = fmaxf(m[c], xor32(m[c]));
+    if (lane < 32) s_max[wave][32 * c + lane] = m[c];
+  }
+  __syncthreads();
+  float c1[QG];
+  bool below = true;
+#pragma unroll
+  for (int c = 0; c < QG; ++c) {
+    const int j = 32 * c + fr;
+    m[c] = fmaxf(fmaxf(s_max[0][j], s_max[1][j]), fmaxf(s_max[2][j], s_max[3][j]));
+    c1[c] = (m[c] == -INFINITY) ? 0.0f
+                                : __builtin_fmaf(-g.c0, m[c], MODE == EXACT ? 0.0f : kK127);
+    below = below && row_c1_below(c1[c]);
+  }
+
+  // ---- pass 2
+  float part[QG];
+  f32x16_t oacc[QG][2];
+#pragma unroll
+  for (int c = 0; c < QG; ++c) {
+    part[c] = 0.0f;
+    oacc[c][0] = f32x16_t{};
+    oacc[c][1] = f32x16_t{};
+  }
+  const int np2 = below ? np : 0;
+  if (np2 > 0) {
+    u32x4_t ka[4], va[2][2];
+    // block i's scores; group c's are replaced by block i + 1's (a copy, 6 % of the
+    // loop's VALU instructions; three accumulators whose roles rotate from block to
+    // block instead of it did not fit 256 registers: 237 spilled)
+    f32x16_t sc[QG];
+    uint32_t pk[QG][4][2];   // block i's (or, where not yet computed, block i - 1's) probabilities
+    wait_loads<4>();         // K blocks 0 and 1
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) ka[ks] = read_k(0, ks);
+#pragma unroll
+    for (int c = 0; c < QG; ++c) {
+      sc[c] = mma<DT>(ka[0], qf[c][0], zero);
+#pragma unroll
+      for (int ks = 1; ks < 4; ++ks) sc[c] = mma<DT>(ka[ks], qf[c][ks], sc[c]);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) ka[ks] = read_k(1, ks);
+    wait_lds();
+    load_k(min(2, np - 1), 0);
+    // O += V^T P, product (ks, db) of group c
+    auto pv = [&](int c, int ks, int db) {
+      const auto s0 = __builtin_amdgcn_permlane32_swap(pk[c][2 * ks][0], pk[c][2 * ks + 1][0],
+                                                       false, false);
+      const auto s1 = __builtin_amdgcn_permlane32_swap(pk[c][2 * ks][1], pk[c][2 * ks + 1][1],
+                                                       false, false);
+      const u32x4_t bv = {s0[0], s1[0], s0[1], s1[1]};
+      oacc[c][db] = mma<DT>(va[ks][db], bv, oacc[c][db]);
+    };
+    auto block = [&](int i, auto first) {
+      constexpr bool FIRST = decltype(first)::value;
+      wait_lds();        // V^T block i - 1 and K block i + 1 have been read
+      wait_loads<4>();   // V^T block i
+      load_v(min(i + 1, np - 1), 2 + ((i + 1) & 1));
+      load_k(min(i + 3, np - 1), (i + 1) & 1);
+#pragma unroll
+      for (int c = 0; c < QG; ++c) {
+        if (c == QG - 1) wait_loads<8>();   // K block i + 2
+        f32x16_t sn;
+        uint32_t pn[4][2];
+        const int pc = c == 0 ? QG - 1 : c - 1;   // whose second product runs beside this
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          sn = mma<DT>(ka[u], qf[c][u], u == 0 ? zero : sn);
+          if (c == QG - 1) ka[u] = read_k(i & 1, u);
+          if (!(FIRST && c == 0)) pv(pc, u >> 1, u & 1);
+          if (c == 0) va[u >> 1][u & 1] = read_v(2 + (i & 1), u >> 1, u & 1);
+          float e[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            e[j] = qexp_row<MODE, true>(sc[c][4 * u + j], g.c0, c1[c]);
+            part[c] += e[j];
+          }
+          pn[u][0] = pack16<DT>(e[0], e[1]);
+          pn[u][1] = pack16<DT>(e[2], e[3]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        sc[c] = sn;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          pk[c][u][0] = pn[u][0];
+          pk[c][u][1] = pn[u][1];
+        }
+      }
+    };
+    block(0, std::true_type{});
+    for (int i = 1; i < np; ++i) block(i, std::false_type{});
+#pragma unroll
+    for (int u = 0; u < 4; ++u) pv(QG - 1, u >> 1, u & 1);
+  }
+  wait_loads<0>();
+  wait_lds();
+  for (int i = np2; i < nlive; ++i) {
+    const int kbg = W * i + wave;
+    u32x4_t ka[4];
+    stage_k(kbg, ka);
+    uint32_t pk[QG][4][2];
+#pragma unroll
+    for (int c = 0; c < QG; ++c) {
+      if (kbg < nkbc[c]) {
+        const f32x16_t sacc = scores(ka, c, kbg);
+#pragma unroll
+        for (int gi = 0; gi < 4; ++gi) {
+          float e[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            e[j] = qexp<MODE>(sacc[4 * gi + j], g.c0, c1[c]);
+            part[c] += e[j];
+          }
+          pk[c][gi][0] = pack16<DT>(e[0], e[1]);
+          pk[c][gi][1] = pack16<DT>(e[2], e[3]);
+        }
+      }
+    }
+    u32x4_t gv[4], va[2][2];
+    uint32_t vo[4];
+    vblock_lane_offsets(lane, g.ldv, vo);
+    vblock_load<VK>(Vt, g.ldv, 32 * kbg, S, VK != kVtFull && 32 * kbg + 32 > S, lane, vo, gv);
+    vblock_store(ring, lane, gv);
+    __builtin_amdgcn_wave_barrier();
+    vblock_read(ring, fr, h, va);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < QG; ++c)
+      if (kbg < nkbc[c]) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const auto s0 = __builtin_amdgcn_permlane32_swap(pk[c][2 * ks][0], pk[c][2 * ks + 1][0],
+                                                           false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(pk[c][2 * ks][1], pk[c][2 * ks + 1][1],
+                                                           false, false);
+          const u32x4_t bv = {s0[0], s1[0], s0[1], s1[1]};
+#pragma unroll
+          for (int db = 0; db < 2; ++db) oacc[c][db] = mma<DT>(va[ks][db], bv, oacc[c][db]);
+        }
+      }
+  }
+
+  attn_finish<DT, W, QG, kPipeSlots * 256>(s_ring, s_sum, oacc, part, m, wave, lane, q0, S,
+                                           g.o + (int64_t)bh * S * kAttnD);
 }
 
 // waves = 4, 8: the one-pass kernel with that many waves; 0: two passes with
@@ -675,7 +1044,12 @@ void launch_attn_vk(int waves, int qg, dim3 grid, hipStream_t s, const AttnArgs&
     hipLaunchKernelGGL((attn_kernel<DT, MODE, VK, 4>), grid, dim3(64 * 4), 0, s, g);
   else if (waves == 8)
     hipLaunchKernelGGL((attn_kernel<DT, MODE, VK, 8>), grid, dim3(64 * 8), 0, s, g);
-  else if (qg == 2)
+  else if constexpr (VK != kVtScalar) {
+    if (qg == 2)
+      hipLaunchKernelGGL((attn_pipe_kernel<DT, MODE, VK>), grid, dim3(kAttnThreads), 0, s, g);
+    else
+      hipLaunchKernelGGL((attn_long_kernel<DT, MODE, VK, 1>), grid, dim3(kAttnThreads), 0, s, g);
+  } else if (qg == 2)
     hipLaunchKernelGGL((attn_long_kernel<DT, MODE, VK, 2>), grid, dim3(kAttnThreads), 0, s, g);
   else
     hipLaunchKernelGGL((attn_long_kernel<DT, MODE, VK, 1>), grid, dim3(kAttnThreads), 0, s, g);
@@ -724,8 +1098,13 @@ extern "C" quake_status quake_attention(const void* q, const void* k, const void
   // one pass with 4 key blocks per wave (128 keys), else two passes
   const int waves = seq <= 512 ? 4 : seq <= kAttnMaxS ? 8 : 0;
   const int64_t tiles2 = (seq + 2 * kAttnQ - 1) / (2 * kAttnQ);   // per head, with two groups
+  // 16-byte rows, and byte offsets within a 64-row block of V^T that fit 32 bits
+  const bool vec = aligned16(vt) && ldv % 8 == 0 && ldv <= (1 << 24);
   const int64_t min_tiles = causal ? kAttnLongQGMinTilesCausal : kAttnLongQGMinTiles;
-  const int qg = (waves == 0 && heads >= (min_tiles + tiles2 - 1) / tiles2) ? 2 : 1;
+  const bool two = vec ? heads >= ((causal ? kAttnPipeMinCausal : kAttnPipeMin) + tiles2 * seq - 1) /
+                                      (tiles2 * seq)
+                       : heads >= (min_tiles + tiles2 - 1) / tiles2;
+  const int qg = waves == 0 && two ? 2 : 1;
   const int64_t tile = kAttnQ * qg;   // queries per workgroup
   const int64_t qtiles = (seq + tile - 1) / tile;
   if (heads > INT32_MAX / qtiles || heads * ldv * kAttnD > INT64_MAX / 4) return QUAKE_EINVAL;
@@ -735,8 +1114,6 @@ extern "C" quake_status quake_attention(const void* q, const void* k, const void
                    (uint32_t)(heads % 8 == 0 ? heads / 8 : 0)};
   const dim3 grid((uint32_t)(heads * qtiles));
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // 16-byte rows, and byte offsets within a 64-row block of V^T that fit 32 bits
-  const bool vec = aligned16(vt) && ldv % 8 == 0 && ldv <= (1 << 24);
   const int vk = !vec ? kVtScalar : (seq % 32 == 0 ? kVtFull : kVtRagged);
   if (dtype == QUAKE_BF16)
     launch_attn<BF16>(mode, vk, waves, qg, grid, s, g);

@@ -84,12 +84,13 @@ __device__ const u32x4 g_zero16 = {0u, 0u, 0u, 0u};
 // 16 bytes per lane from each lane's p to LDS bytes lds + 16 * lane (lds
 // uniform). The asm has no register result: the data is in LDS once vmcnt says
 // so. (Issued through the builtin, every later LDS read would wait for every
-// such load, as the compiler does not tell the stages apart.)
+// such load, as the compiler does not tell the stages apart. M0 is used by
+// nothing else here.)
 __device__ __forceinline__ void lds_load16(uint32_t lds, const char* p) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :
                : "s"(lds), "v"(p)
-               : "memory", "m0");
+               : "memory");
 }
 // at most N vector memory operations of this wave still in flight
 template <int N>

@@ -247,6 +247,38 @@ def test_two_group_and_one_group_give_the_same_bits(q, causal):
         assert torch.equal(one[0].view(torch.int16), whole[hd].view(torch.int16)), hd
 
 
+def _pipelined_heads(seq, causal):
+    """The fewest heads for which rows of V^T of 16-byte vectors take the
+    pipelined two-pass kernel: tiles of 64 queries times keys at least 2^18
+    without the mask, 2^20 with it."""
+    return -(-(1 << (20 if causal else 18)) // (-(-seq // 64) * seq))
+
+
+# the pipelined kernel against the one-group kernel on the same heads, bit for
+# bit: every count of key blocks mod 4 (its waves take 8 to 17 blocks), whole and
+# ragged last blocks and query groups, padded rows of V^T with NaN past the
+# keys, and scores past the folded clamp's range (scale 1e5: |c1| > 2^54), where
+# it takes the unpipelined code for every block
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("seq,ldv,dt,mode,scale", [
+    (1032, 1032, "bf16", 2, 1.0), (1056, 1056, "f16", 2, 1.0), (1088, 1088, "bf16", 0, 1.0),
+    (1100, 1104, "f16", 1, 1.0), (1127, 1136, "bf16", 3, 1.0), (1184, 1184, "bf16", 2, 1e5),
+    (1208, 1208, "bf16", 2, 1e5), (2056, 2064, "bf16", 2, 1.0)])
+def test_pipelined_and_one_group_give_the_same_bits(q, causal, seq, ldv, dt, mode, scale):
+    heads = _pipelined_heads(seq, causal)
+    say("attention pipelined vs one-group", heads, seq, ldv, dt, mode, scale, causal)
+    qc, kc, vtc = synth.attention_inputs(heads, seq, 90 + seq % 7, ldv=ldv, pad=float("nan"), dt=dt)
+    qg, kg, vtg = (qc * scale).to("cuda:0"), (kc * scale).to("cuda:0"), vtc.to("cuda:0")
+    whole = q.quake_attention(qg, kg, vtg[:, :, :seq], mode=mode, t=T, causal=causal)
+    # |t m| is about 1e10 at scale 1e5, past the 1e9 up to which the folded row
+    # constant is specified: rows may be NaN there, on both paths alike
+    assert scale > 1.0 or not torch.isnan(whole).any()
+    for hd in sorted({0, heads // 2, heads - 1}):
+        one = q.quake_attention(qg[hd:hd + 1].contiguous(), kg[hd:hd + 1].contiguous(),
+                                vtg[hd:hd + 1].contiguous()[:, :, :seq], mode=mode, t=T, causal=causal)
+        assert torch.equal(one[0].view(torch.int16), whole[hd].view(torch.int16)), hd
+
+
 @pytest.mark.parametrize("seq,ldv", [(777, 781), (777, 784), (1111, 1115), (2100, 2103),
                                      (2100, 2104)])
 @pytest.mark.parametrize("causal", [True, False])
