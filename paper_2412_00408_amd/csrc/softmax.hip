@@ -131,14 +131,23 @@ struct CausalArg {
   uint32_t row0_mod, period;
   int64_t shift;
   uint32_t write_masked;   // 0: masked outputs are not stored
+  uint32_t inv;            // floor(2^32 / period), at most 2^32 - 1
 };
+
+// n mod period. q = floor(n inv / 2^32) is at most 2 below floor(n / period):
+// inv > 2^32 / period - 1 (for period 1 too), so n inv / 2^32 > n / period - 1.
+__device__ __forceinline__ uint32_t mod_period(uint32_t n, const CausalArg& ca) {
+  uint32_t r = n - (uint32_t)(((uint64_t)n * ca.inv) >> 32) * ca.period;
+  r = r >= ca.period ? r - ca.period : r;
+  return r >= ca.period ? r - ca.period : r;
+}
 
 template <bool CAUSAL>
 __device__ __forceinline__ int64_t live_len(const CausalArg& ca, uint32_t local_row, int64_t cols) {
   if constexpr (!CAUSAL) {
     return cols;
   } else {
-    const int64_t r = (int64_t)((ca.row0_mod + local_row) % ca.period);
+    const int64_t r = (int64_t)mod_period(ca.row0_mod + local_row, ca);
     const int64_t L = r + ca.shift + 1;
     return L < 0 ? 0 : (L > cols ? cols : L);
   }
@@ -183,6 +192,32 @@ __device__ __forceinline__ void store_inside(char* ya, uint32_t vi, uint32_t s, 
   }
 }
 
+// The same for a row whose offset s is uniform across the wave, by at most three
+// naturally aligned stores each (the first vector's bytes from b on, the last
+// vector's first t bytes; b and t uniform, so which of them are made is a
+// scalar branch). Element by element, the two ends of a row were 70 of the 305
+// VALU instructions of a 1001-element bf16 row. One lane is active.
+__device__ __forceinline__ uint32_t word_at(const u32x4 p, uint32_t byte) {
+  const uint32_t lo = (byte & 4) ? p[1] : p[0], hi = (byte & 4) ? p[3] : p[2];
+  return (byte & 8) ? hi : lo;
+}
+__device__ __forceinline__ void store_from(char* v, uint32_t b, const u32x4 p) {
+  if (b & 2) {
+    *reinterpret_cast<uint16_t*>(v + b) = (uint16_t)(word_at(p, b) >> 16);
+    b += 2;
+  }
+  if (b & 4) {
+    *reinterpret_cast<uint32_t*>(v + b) = word_at(p, b);
+    b += 4;
+  }
+  if (b & 8) *reinterpret_cast<uint2*>(v + 8) = uint2{p[2], p[3]};
+}
+__device__ __forceinline__ void store_until(char* v, uint32_t t, const u32x4 p) {
+  if (t & 8) *reinterpret_cast<uint2*>(v) = uint2{p[0], p[1]};
+  if (t & 4) *reinterpret_cast<uint32_t*>(v + (t & 8)) = word_at(p, t & 8);
+  if (t & 2) *reinterpret_cast<uint16_t*>(v + (t & 12)) = (uint16_t)word_at(p, t & 12);
+}
+
 // ---------------------------------------------------------------------------
 // Register-resident rows: one wave (WAVES = 1) or one workgroup (WAVES = 4).
 // ---------------------------------------------------------------------------
@@ -203,8 +238,10 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int lid = threadIdx.x % LANES;
-  const uint32_t row = blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LANES;
-  if (WAVES == 1 && row >= rows) return;   // uniform per wave
+  // uniform per wave (said so to the compiler: the row's bases and live length
+  // stay in scalar registers)
+  const uint32_t row = __builtin_amdgcn_readfirstlane(blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LANES);
+  if (WAVES == 1 && row >= rows) return;
 
   // SHIFT: nvr carries the row length in elements; the row is read as the
   // aligned vectors that cover it (x and y rows share their offset s).
@@ -231,6 +268,17 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   const uint32_t L = (uint32_t)live_len<CAUSAL>(ca, row, SHIFT ? (int64_t)cols : (int64_t)nvr * V);
   const uint32_t nvl = !CAUSAL ? nvr : L == 0 ? 0 : (s + L + V - 1) / V;
   const uint32_t vlast = (nvl > 0 ? nvl : 1) - 1;
+  // With the mask, a wave's k-th group of vectors that lies wholly past the
+  // live entries (uniform) is neither computed nor summed (every term would be
+  // +0: the same bits), and only the vectors at the ends of the live range are
+  // masked element by element. About half of the groups of a causal block go.
+  // bf16 96096 x 1001 (period 1001) was bound by VALU issue (98 % of its
+  // cycles): 58.1 -> 54.0 us with these, the uniform row and the row ends stored
+  // in at most three pieces (288 MB, 5.3 TB/s; the folded clamp and a cheaper
+  // boundary mask on top of it gave nothing more).
+  const uint32_t wave_v = __builtin_amdgcn_readfirstlane(lid);   // the wave's first vector, group 0
+  const uint32_t nvl_u = CAUSAL ? (uint32_t)__builtin_amdgcn_readfirstlane(nvl) : 0;
+  auto live = [&](int k) { return !CAUSAL || k == 0 || k * LANES + wave_v < nvl_u; };
   u32x4 raw[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k)
@@ -240,6 +288,7 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const uint32_t vi = k * LANES + lid;
+    if (!live(k)) continue;
     // whole vectors past the row end become -inf before widening (one select
     // per word); only the causal boundary needs a per-element mask
     if (!FULL && !CAUSAL && vi >= nvr) raw[k] = neg_inf_vec<DT>();
@@ -247,12 +296,15 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
     if constexpr (SHIFT && !CAUSAL) {
       if (vi == 0 || vi + 1 == nvr) mask_outside<V>(f[k], vi, s, cols);
     }
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
+    if constexpr (CAUSAL) {
       // with SHIFT, elements before the row start wrap to large values
-      if constexpr (CAUSAL) f[k][j] = (vi * V + j - s < L) ? f[k][j] : -INFINITY;
-      lmax = fmaxf(lmax, f[k][j]);
+      if ((SHIFT && vi == 0) || vi * V + V > s + L) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) f[k][j] = (vi * V + j - s < L) ? f[k][j] : -INFINITY;
+      }
     }
+#pragma unroll
+    for (int j = 0; j < V; ++j) lmax = fmaxf(lmax, f[k][j]);
   }
 
   float m = wave_max(lmax);
@@ -268,6 +320,7 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   Acc acc = 0;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
+    if (!live(k)) continue;
     f[k][0] = ex(f[k][0]);
     float part = f[k][0];
 #pragma unroll
@@ -289,12 +342,23 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   for (int k = 0; k < NV; ++k) {
     const uint32_t vi = k * LANES + lid;
     if ((FULL || vi < nvr) && (!CAUSAL || ca.write_masked || vi < nvl)) {
+      const bool some = live(k);
 #pragma unroll
-      for (int j = 0; j < V; ++j) f[k][j] *= r;
-      if (SHIFT && (vi == 0 || vi + 1 == nvr))
-        store_inside<DT>(yrow, vi, s, cols, f[k]);
-      else
+      for (int j = 0; j < V; ++j) f[k][j] = some ? f[k][j] * r : 0.0f;
+      if constexpr (!SHIFT) {
         __builtin_nontemporal_store(pack<DT>(f[k]), yr + vi);
+      } else {
+        const uint32_t t = (s + cols) * kEsz<DT> & 15u;   // bytes of the last vector, 0: all
+        const bool first = vi == 0 && s != 0, last = vi + 1 == nvr && t != 0;
+        if (first && last) {
+          store_inside<DT>(yrow, vi, s, cols, f[k]);
+        } else {
+          const u32x4 p = pack<DT>(f[k]);
+          if (first) store_from(yrow, s * kEsz<DT>, p);
+          else if (last) store_until(yrow + 16 * (size_t)vi, t, p);
+          else __builtin_nontemporal_store(p, yr + vi);
+        }
+      }
     }
   }
 }
@@ -1018,8 +1082,10 @@ struct SmArgs {
 };
 
 static CausalArg causal_at(const SmArgs& a, int64_t r0) {
-  if (a.period <= 0) return CausalArg{0, 1, 0, 1};
-  return CausalArg{(uint32_t)(r0 % a.period), (uint32_t)a.period, a.shift, a.write_masked};
+  if (a.period <= 0) return CausalArg{0, 1, 0, 1, UINT32_MAX};
+  const uint64_t inv = (uint64_t(1) << 32) / (uint64_t)a.period;
+  return CausalArg{(uint32_t)(r0 % a.period), (uint32_t)a.period, a.shift, a.write_masked,
+                   (uint32_t)std::min<uint64_t>(inv, UINT32_MAX)};
 }
 
 constexpr int64_t kRowChunk = int64_t(1) << 28;   // rows per launch (grid stays < 2^31)

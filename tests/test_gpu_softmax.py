@@ -417,6 +417,53 @@ def test_causal_without_masked_writes(q, cols, dt):
     assert np.all(gv[written & ~live] == 0.0)
 
 
+# live lengths on both sides of a wave's 64-vector groups (whole groups past the
+# live entries are skipped), rows at every offset from 16 bytes with padding
+# between them that must stay as it was (row ends stored in pieces), and NaN in
+# the masked half, which is never used
+@pytest.mark.parametrize("cols,dt", [(1001, "bf16"), (517, "f32"), (2047, "f16"), (3001, "f32"),
+                                     (9000, "bf16"), (9, "f32"), (17, "f16"), (5, "bf16")])
+@pytest.mark.parametrize("write_masked", [True, False])
+def test_causal_groups_and_row_ends(q, cols, dt, write_masked):
+    vec, rows = (4 if dt == "f32" else 8), 43
+    for end, pad, off in [(64 * vec, 3, 1), (128 * vec, 1, 0), (cols, 5, 2), (1, 2, 3)]:
+        shift = min(end, cols) - 22          # live lengths end - 21 .. end + 21, clipped
+        say("softmax causal groups", dt, cols, end, pad, off, write_masked)
+        x = synth.normal((rows, cols), 2.0, dt, 1180 + cols % 61)
+        ref = oracle.softmax_causal(host_bits(x), rows, shift, dt, 2, t=0.9, threads=THREADS)
+        live = np.arange(cols)[None, :] <= np.arange(rows)[:, None] + shift
+        xm = x.clone()
+        xm[torch.from_numpy(~live)] = float("nan")
+        ld = cols + pad
+        xb = torch.full((off + rows * ld,), float("nan"), dtype=x.dtype)
+        xb[off:].view(rows, ld)[:, :cols] = xm
+        yb = torch.full((off + rows * ld,), 7.0, dtype=x.dtype, device="cuda:0")
+        yv = yb[off:].view(rows, ld)
+        q.quake_softmax_causal(xb.to("cuda:0")[off:].view(rows, ld)[:, :cols], yv[:, :cols],
+                               period=rows, shift=shift, mode=2, t=0.9, write_masked=write_masked)
+        torch.cuda.synchronize()
+        assert (yb[:off] == 7.0).all() and (yv[:, cols:] == 7.0).all(), "writes outside the rows"
+        g = host_bits(yv[:, :cols].contiguous())
+        assert_parity(g[live], ref[live], dt, "op", "causal groups %s %d" % (dt, cols))
+        gm = oracle.decode(g.reshape(-1), dt).reshape(rows, cols)[~live]
+        assert np.all(gm == 0.0) if write_masked else np.all((gm == 0.0) | (gm == 7.0))
+
+
+def test_period_remainder_by_multiplication():
+    """The causal kernels' row mod period: q = floor(n floor(2^32 / p) / 2^32) and
+    two conditional subtractions, against % over its whole range (n < 2^32)."""
+    r = np.random.default_rng(5)
+    p = np.r_[1, 2, 3, 7, 512, 1001, 2**16, 2**16 + 1, 2**30, 2**31 - 1,
+              r.integers(1, 2**31, 4000)].astype(np.uint64)
+    n = np.r_[0, 1, 2**31, 2**32 - 1, r.integers(0, 2**32, 400)].astype(np.uint64)[:, None]
+    n = np.concatenate([np.broadcast_to(n, (len(n), len(p))), p[None] - 1, p[None], 2 * p[None] - 1])
+    inv = np.minimum((1 << 32) // p, (1 << 32) - 1).astype(np.uint64)
+    m = n - ((n * inv) >> np.uint64(32)) * p
+    for _ in range(2):
+        m = np.where(m >= p, m - p, m)
+    assert (m == n % p).all()
+
+
 # Square causal blocks (period = cols, shift = 0, at most 64 vectors per row)
 # take the paired-row kernel: two rows per wave, r and M - 1 - r. Shapes cover
 # K = 0 and K > 0 (P above 63 vectors), odd M, one-vector rows, a trailing
