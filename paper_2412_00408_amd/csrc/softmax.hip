@@ -238,9 +238,11 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int lid = threadIdx.x % LANES;
-  // uniform per wave (said so to the compiler: the row's bases and live length
-  // stay in scalar registers)
-  const uint32_t row = __builtin_amdgcn_readfirstlane(blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LANES);
+  // uniform per wave, and said so to the compiler: the row's bases and live length
+  // stay in scalar registers (whole aligned rows of a workgroup, 8192 x 8192
+  // binary32, were 5 % slower that way)
+  const uint32_t row = WAVES == 1 || SHIFT ? __builtin_amdgcn_readfirstlane(blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LANES)
+                                           : blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LANES;
   if (WAVES == 1 && row >= rows) return;
 
   // SHIFT: nvr carries the row length in elements; the row is read as the
@@ -276,9 +278,12 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   // cycles): 58.1 -> 54.0 us with these, the uniform row and the row ends stored
   // in at most three pieces (288 MB, 5.3 TB/s; the folded clamp and a cheaper
   // boundary mask on top of it gave nothing more).
+  // Not for rows that their memory time bounds (binary32, and aligned rows of a
+  // workgroup, below 8 groups): 2 % slower there.
+  constexpr bool kSkip = CAUSAL && (NV >= 8 || (DT != F32 && (WAVES == 1 || SHIFT)));
   const uint32_t wave_v = __builtin_amdgcn_readfirstlane(lid);   // the wave's first vector, group 0
-  const uint32_t nvl_u = CAUSAL ? (uint32_t)__builtin_amdgcn_readfirstlane(nvl) : 0;
-  auto live = [&](int k) { return !CAUSAL || k == 0 || k * LANES + wave_v < nvl_u; };
+  const uint32_t nvl_u = kSkip ? (uint32_t)__builtin_amdgcn_readfirstlane(nvl) : 0;
+  auto live = [&](int k) { return !kSkip || k == 0 || k * LANES + wave_v < nvl_u; };
   u32x4 raw[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k)
@@ -298,7 +303,7 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
     }
     if constexpr (CAUSAL) {
       // with SHIFT, elements before the row start wrap to large values
-      if ((SHIFT && vi == 0) || vi * V + V > s + L) {
+      if (!kSkip || (SHIFT && vi == 0) || vi * V + V > s + L) {
 #pragma unroll
         for (int j = 0; j < V; ++j) f[k][j] = (vi * V + j - s < L) ? f[k][j] : -INFINITY;
       }
