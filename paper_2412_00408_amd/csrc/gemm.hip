@@ -362,33 +362,36 @@ void launch_tile(GemmArgs g, hipStream_t s) {
 // need the least operand traffic, small ones fill the chip where m n is small;
 // the estimate picks between them. Over 70 random shapes (m to 16384, n to
 // 4096, k to 4096) the picks took 1.9 % longer than the best of sixteen
-// tiles measured on each.
+// tiles measured on each. A launch takes fewer than 2^32 threads: a tile whose
+// grid has more is passed over (only past 2^30 rows; 128 x 128 and the larger
+// ones have 512 threads, the others 256).
 struct Tile {
-  int bm, bn, per_cu;
+  int bm, bn, threads, per_cu;
   float fixed, again, slab1, slab;
 };
 constexpr Tile kTiles[] = {
-    {256, 256, 1, 13.0f, 8.3f, 1.30f, 1.30f},
-    {256, 192, 1, 11.0f, 6.6f, 1.01f, 1.01f},
-    {128, 128, 1, 5.9f, 4.1f, 0.44f, 0.44f},
-    {128, 64, 2, 4.2f, 2.5f, 0.32f, 0.56f},
-    {64, 64, 2, 3.7f, 1.5f, 0.19f, 0.37f},
-    {64, 32, 1, 3.6f, 2.2f, 0.155f, 0.155f},
+    {256, 256, 512, 1, 13.0f, 8.3f, 1.30f, 1.30f},
+    {256, 192, 512, 1, 11.0f, 6.6f, 1.01f, 1.01f},
+    {128, 128, 512, 1, 5.9f, 4.1f, 0.44f, 0.44f},
+    {128, 64, 256, 2, 4.2f, 2.5f, 0.32f, 0.56f},
+    {64, 64, 256, 2, 3.7f, 1.5f, 0.19f, 0.37f},
+    {64, 32, 256, 1, 3.6f, 2.2f, 0.155f, 0.155f},
 };
 
 inline int pick_tile(int64_t m, int64_t n, int64_t k, int cus) {
   const double slabs = (double)((k + kBK - 1) / kBK);
-  int best = 0;
-  double best_us = 0;
+  int best = 0;   // where no tile's grid can be launched: the launch reports it
+  double best_us = -1;
   for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
     const Tile& t = kTiles[i];
     const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn);
+    if (tiles * t.threads > (int64_t)UINT32_MAX) continue;
     const int64_t slots = (int64_t)t.per_cu * cus;
     const int64_t full = tiles / slots, rest = tiles % slots;
     const double rounds = (double)(full + (rest != 0));
     const double us = t.fixed + (rounds - 1) * t.again + (double)full * slabs * t.slab +
                       (rest == 0 ? 0.0 : slabs * (rest <= cus ? t.slab1 : t.slab));
-    if (i == 0 || us < best_us) {
+    if (best_us < 0 || us < best_us) {
       best = i;
       best_us = us;
     }

@@ -342,6 +342,7 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
     total = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
   }
   const float r = (m == -INFINITY) ? 0.0f : inv_total(total);
+  const float none = 0.0f * r;   // an entry not computed: NaN where a live NaN or inf made r so
 
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
     if ((FULL || vi < nvr) && (!CAUSAL || ca.write_masked || vi < nvl)) {
       const bool some = live(k);
 #pragma unroll
-      for (int j = 0; j < V; ++j) f[k][j] = some ? f[k][j] * r : 0.0f;
+      for (int j = 0; j < V; ++j) f[k][j] = some ? f[k][j] * r : none;
       if constexpr (!SHIFT) {
         __builtin_nontemporal_store(pack<DT>(f[k]), yr + vi);
       } else {
