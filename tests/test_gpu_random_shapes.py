@@ -221,7 +221,7 @@ def test_random_elementwise_offsets(q, op, n, dt, xoff, yoff, seed):
 
 def _linear_cases(n, seed):
     """(m, n, k, mode, dt, gelu, pad, seed): output widths around multiples
-    of 128 and 192 (grids this small take the 128-wide tile), ragged m and n,
+    of 128 and 192, ragged m and n,
     k a multiple of 8 from one slab to several with a tail, operand rows
     padded to a longer stride."""
     rng = np.random.default_rng(seed)
