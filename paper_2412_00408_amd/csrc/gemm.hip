@@ -24,9 +24,10 @@
 //  * Latency. The x and w tiles have SA and SB stages in LDS (up to 160 KB), so
 //    that a slab is loaded one to four slabs ahead; one barrier per slab.
 //  * The output. Tiles end together, so the write is not hidden; it leaves
-//    through LDS as whole rows, 16 bytes per lane, and non-temporally, so that
-//    L2 has little left to write back at the end of the kernel (the product of
-//    16384 x 4096 x 1024: 126.8 -> 112.1 us).
+//    through LDS as whole rows, 16 bytes per lane at any address of y (rows of
+//    y are 16-byte aligned only where n is a multiple of 8). Aligned rows are
+//    written non-temporally, so that L2 has little left to write back at the
+//    end of the kernel (the product of 16384 x 4096 x 1024: 126.8 -> 112.1 us).
 // Measured against the kernel this replaced (128-wide tiles of 32 x 32 blocks,
 // slabs through registers; back to back, with the GELU): bf16 4096 x 3072 x 768
 // 26.5 -> 21.9 us, 4096 x 768 x 3072 (no GELU) 37.2 -> 22.3 us, binary16
@@ -122,6 +123,27 @@ __device__ __forceinline__ uint2 gelu4(f32x4_t v, const GemmArgs& g, int op) {
   return o;
 }
 
+// Stores to y at any address: gfx950 takes vector stores there (the compiler
+// emits the same global_store_dwordx4 for this type). Unaligned rows cost 0-9 %
+// more than aligned ones that way; element by element they cost 24-43 % more
+// (13020 x 1666 x 128: 37.6 -> 24.6 us, 10308 x 3341 x 360: 72.7 -> 53.4, 2045 x 3069
+// x 200: 14.7 -> 12.0; put together from dwords of LDS to aligned vectors and 2-byte
+// row ends, 13020 x 1666 x 128 took as long as this and 6469 x 4028 x 72 10 % more).
+// Not non-temporal: their vectors share lines with the next tile's, which L2 has
+// to merge (8210 x 3081 x 16: 27.5 against 38.4 us).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+// the first n (1 to 7) elements of v to p
+__device__ __forceinline__ void store_head(uint16_t* p, uint32_t n, const u32x4 v) {
+  if (n & 4) *reinterpret_cast<u32x2_any*>(p) = u32x2_any{v[0], v[1]};
+  if (n & 2) *reinterpret_cast<u32_any*>(p + (n & 4)) = (n & 4) ? v[2] : v[0];
+  if (n & 1)
+    *reinterpret_cast<u16_any*>(p + (n & 6)) =
+        (uint16_t)((n & 4) ? ((n & 2) ? v[3] : v[2]) : ((n & 2) ? v[1] : v[0]));
+}
+
 // WM x WN waves over a BM x BN tile, SA / SB stages of its x / w slab
 // (|SA - SB| <= 1); registers for two waves per SIMD.
 template <int DT, int BM, int BN, int WM, int WN, int SA, int SB>
@@ -137,7 +159,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && NW % 2 == 0, "whole loads per wave");
   static_assert(BM % (32 * WM) == 0 && BN % (16 * WN) == 0, "whole blocks per wave");
   static_assert(SA >= 2 && SB >= 2 && SA - SB <= 1 && SB - SA <= 1, "stages");
-  static_assert(NW * 64 * P <= kLds && kLds <= 163840, "LDS");
+  constexpr int H = NW * 64 * P <= kLds ? 2 : 1;              // staging areas per wave, used in turn
+  static_assert(H * NW * 32 * P <= kLds && kLds <= 163840, "LDS");
   __shared__ __attribute__((aligned(16))) char smem[kLds];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   const int lane = threadIdx.x & 63;
@@ -294,15 +317,17 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
 
   // Epilogue: GELU on the binary32 accumulators, rounded to the 16-bit format,
   // two rows of blocks (32 rows of y) at a time through this wave's own LDS
-  // (two halves in turn) to whole rows. Accumulator r of block (i, j) in lane l
-  // is row 16 i + l mod 16, column 16 j + 4 (l / 16) + r of the wave's part.
+  // to whole rows. Accumulator r of block (i, j) in lane l is row 16 i + l mod 16,
+  // column 16 j + 4 (l / 16) + r of the wave's part. All of a pass's LDS reads
+  // stand before its first store (a store under the row guard ends a basic
+  // block, so that a read after it would be waited for alone).
   __syncthreads();
   constexpr int CH = TN * 2;   // 16-byte vectors per row
   const int wrow = row0 + wm * TM * 16, wcol = col0 + wn * TN * 16;
   auto epilogue = [&](auto op) {
 #pragma unroll
     for (int i = 0; i < TM; i += 2) {
-      char* st = smem + (2 * wave + ((i >> 1) & 1)) * (32 * P);
+      char* st = smem + (H * wave + (i >> 1) % H) * (32 * P);
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -310,30 +335,21 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
           *reinterpret_cast<uint2*>(st + (16 * u + fr) * P + 32 * j + 8 * h) =
               gelu4<DT>(acc[i + u][j], g, decltype(op)::value);
       __builtin_amdgcn_wave_barrier();
-      if (g.vec) {
+      u32x4 v[TN];
 #pragma unroll
-        for (int q = 0; q < 32 * CH / 64; ++q) {
-          const int c = q * 64 + lane, rr = c / CH, cc = c % CH;
-          const u32x4 v = *reinterpret_cast<const u32x4*>(st + rr * P + 16 * cc);
-          const uint32_t row = wrow + 16 * i + rr, col = wcol + 8 * cc;
-          if (row >= (uint32_t)g.m) continue;
-          uint16_t* yr = g.y + (int64_t)row * g.ldy + col;
-          if (col + 8 <= (uint32_t)g.n)
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(yr));
-          else
+      for (int q = 0; q < TN; ++q) {
+        const int c = q * 64 + lane;
+        v[q] = *reinterpret_cast<const u32x4*>(st + c / CH * P + 16 * (c % CH));
+      }
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (col + e < (uint32_t)g.n) yr[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-        }
-      } else {
-        // rows of any alignment: one element per lane, 128 bytes of a row at a time
-#pragma unroll 4
-        for (int q = 0; q < 32 * TN * 16 / 64; ++q) {
-          const int c = q * 64 + lane, rr = c / (TN * 16), cc = c % (TN * 16);
-          const uint16_t v = *reinterpret_cast<const uint16_t*>(st + rr * P + 2 * cc);
-          const uint32_t row = wrow + 16 * i + rr, col = wcol + cc;
-          if (row < (uint32_t)g.m && col < (uint32_t)g.n) g.y[(int64_t)row * g.ldy + col] = v;
-        }
+      for (int q = 0; q < TN; ++q) {
+        const int c = q * 64 + lane;
+        const uint32_t row = wrow + 16 * i + c / CH, col = wcol + 8 * (c % CH);
+        if (row >= (uint32_t)g.m || col >= (uint32_t)g.n) continue;
+        uint16_t* yr = g.y + (int64_t)row * g.ldy + col;
+        if (col + 8 > (uint32_t)g.n) store_head(yr, g.n - col, v[q]);
+        else if (g.vec) __builtin_nontemporal_store(v[q], reinterpret_cast<u32x4*>(yr));
+        else *reinterpret_cast<u32x4_any*>(yr) = v[q];
       }
       __builtin_amdgcn_wave_barrier();
     }

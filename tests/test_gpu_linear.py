@@ -133,6 +133,69 @@ def test_every_tile(q, m, n, k, dt):
                "linear tile %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
 
 
+# Rows of y at every offset from 16 bytes, in rows wider than n: the last vector
+# of a row holds 1 to 8 of its elements (n mod 8) on each tile that small shapes
+# reach, and nothing is written before, between and after the rows.
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (3, 5), (6, 2), (0, 8), (7, 1)])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_rows_of_y_at_any_offset(q, off, pad, dt):
+    for m, k in ((75, 136), (1100, 64)):
+        for n in (1, 7, 66, 195, 257, 300, 604, 797):
+            say("linear y offset", dt, m, n, k, off, pad)
+            x = synth.normal((m, k), 1.0, dt, 1950 + n)
+            w = synth.normal((n, k), 0.05, dt, 1960 + n)
+            ld = n + pad
+            buf = torch.full((off + m * ld + 9,), 7.0, dtype=x.dtype, device="cuda:0")
+            rows = buf[off:off + m * ld].view(m, ld)
+            q.quake_linear_gelu(x.to("cuda:0"), w.to("cuda:0"), y=rows[:, :n], mode=2)
+            torch.cuda.synchronize()
+            assert (buf[:off] == 7.0).all() and (buf[off + m * ld:] == 7.0).all(), "writes outside y"
+            assert (rows[:, n:] == 7.0).all(), "writes between the rows"
+            xb, wb = host_bits(x), host_bits(w)
+            ref = oracle.linear_gelu(xb, wb, 2, gelu=True, dt=dt, threads=THREADS)
+            _check(host_bits(rows[:, :n].contiguous()), ref, xb, wb, k, 2.0,
+                   "linear y offset %s %dx%dx%d off %d pad %d" % (dt, m, n, k, off, pad), dt)
+
+
+def _graph_us(fn, calls=20):
+    """Microseconds per call, the least of seven replays of a graph of calls."""
+    fn()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(calls):
+            fn()
+    g.replay()
+    t = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        g.replay()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) * 1e3 / calls)
+    return min(t)
+
+
+def test_unaligned_rows_take_no_longer(q):
+    """Rows of y that are not 16-byte aligned (n mod 8 != 0) against the next
+    larger multiple of 8, over shapes whose output is much of their time. The
+    geometric mean of the five ratios was 1.35 with 2-byte stores and is 1.02-1.08
+    with vectors at any address; runs differ by 2-4 %, and the bound is halfway."""
+    ratio = 1.0
+    for m, n, k in ((8210, 3081, 72), (13020, 1666, 128), (10308, 3341, 360), (4096, 3071, 768),
+                    (2045, 3069, 200)):
+        us = []
+        for nn in (n, (n + 7) // 8 * 8):
+            x = torch.randn(m, k, device="cuda:0").bfloat16()
+            w = (torch.randn(nn, k, device="cuda:0") / k ** 0.5).bfloat16()
+            y = torch.empty((m, nn), dtype=x.dtype, device="cuda:0")
+            us.append(_graph_us(lambda: q.quake_linear_gelu(x, w, y=y)))
+        say("linear unaligned rows", m, n, k, "%.2f us, aligned %.2f us" % tuple(us))
+        ratio *= us[0] / us[1]
+    assert ratio ** 0.2 < 1.18, ratio ** 0.2
+
+
 def test_strided_rows(q):
     say("linear gelu strided")
     g, r, xb, wb = _run(q, 256, 256, 768, 2, True, 1700, pad=24)
