@@ -23,14 +23,21 @@
 //    bursts, 109 us with the loads spread out; 100 us with 16 x 16 blocks).
 //  * Latency. The x and w tiles have SA and SB stages in LDS (up to 160 KB), so
 //    that a slab is loaded one to four slabs ahead; one barrier per slab.
-//  * The output. Tiles end together, so the write is not hidden; it leaves
+//  * The output. Where tiles end together, the write is not hidden; it leaves
 //    through LDS as whole rows, 16 bytes per lane at any address of y (rows of
-//    y are 16-byte aligned only where n is a multiple of 8). Aligned rows are
-//    written non-temporally, so that L2 has little left to write back at the
-//    end of the kernel (the product of 16384 x 4096 x 1024: 126.8 -> 112.1 us).
+//    y are 16-byte aligned only where n is a multiple of 8). Of aligned rows a
+//    large output is written non-temporally, so that L2 has little left to
+//    write back at the end of the kernel (the product of 16384 x 4096 x 1024:
+//    126.8 -> 112.1 us).
+//  * Few slabs. The first slab and the output then take most of a tile's time,
+//    and only other workgroups of the same CU can hide them: small tiles, and
+//    128 x 128 with two or three stages instead of five, of which two fit a
+//    CU. With k of one slab a tile has one stage and no refills (with two or
+//    three, whose loads past the end of k fetch zeros, such products took 8 %
+//    longer over 300 shapes, 12436 x 3713 x 64 37 against 33 us).
 // Measured against the kernel this replaced (128-wide tiles of 32 x 32 blocks,
 // slabs through registers; back to back, with the GELU): bf16 4096 x 3072 x 768
-// 26.5 -> 21.9 us, 4096 x 768 x 3072 (no GELU) 37.2 -> 22.3 us, binary16
+// 26.5 -> 21.9 us, 4096 x 768 x 3072 (no GELU) 37.2 -> 21.0 us, binary16
 // 16384 x 4096 x 1024 (EXACT) 187.0 -> 129.0 us (1065 TFLOP/s).
 //
 // Operand lane layout of the 16x16x32 16-bit MFMA: lane l holds row l mod 16
@@ -76,7 +83,7 @@ struct GemmArgs {
   float c0, c1, a;         // GELU constants (Eq. 7 folded into Eq. 5)
   uint32_t tiles_m, tiles_n;
   int32_t op;              // quake_mode of the GELU, or -1 for the product alone
-  uint32_t vec;            // rows of y are 16-byte aligned
+  uint32_t nt;             // y (rows 16-byte aligned) is written non-temporally
 };
 
 // where lanes past the end of k load from
@@ -145,7 +152,8 @@ __device__ __forceinline__ void store_head(uint16_t* p, uint32_t n, const u32x4 
 }
 
 // WM x WN waves over a BM x BN tile, SA / SB stages of its x / w slab
-// (|SA - SB| <= 1); registers for two waves per SIMD.
+// (|SA - SB| <= 1, both at least 2; or one each, for k of one slab, where
+// nothing is refilled); registers for two waves per SIMD.
 template <int DT, int BM, int BN, int WM, int WN, int SA, int SB>
 __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
   constexpr int NW = WM * WN;
@@ -155,12 +163,14 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
   constexpr uint32_t kA = BM * kSlabRow, kB = BN * kSlabRow;  // bytes of a stage
   constexpr uint32_t kB0 = SA * kA;                           // first w stage
   constexpr int P = TN * 32 + 16;                             // row pitch of the epilogue's staging
-  constexpr int kLds = SA * BM * kSlabRow + SB * BN * kSlabRow;
+  constexpr bool kOne = SA == 1 && SB == 1;
+  constexpr int kSlabs = SA * BM * kSlabRow + SB * BN * kSlabRow;
+  constexpr int H = NW * 64 * P <= kSlabs ? 2 : 1;            // staging areas per wave, used in turn
+  constexpr int kLds = kSlabs > H * NW * 32 * P ? kSlabs : H * NW * 32 * P;
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && NW % 2 == 0, "whole loads per wave");
   static_assert(BM % (32 * WM) == 0 && BN % (16 * WN) == 0, "whole blocks per wave");
-  static_assert(SA >= 2 && SB >= 2 && SA - SB <= 1 && SB - SA <= 1, "stages");
-  constexpr int H = NW * 64 * P <= kLds ? 2 : 1;              // staging areas per wave, used in turn
-  static_assert(H * NW * 32 * P <= kLds && kLds <= 163840, "LDS");
+  static_assert(kOne || (SA >= 2 && SB >= 2 && SA - SB <= 1 && SB - SA <= 1), "stages");
+  static_assert(kLds <= 163840, "LDS");
   __shared__ __attribute__((aligned(16))) char smem[kLds];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   const int lane = threadIdx.x & 63;
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
   // of the slab are done there, the next slab has landed, and the slab's
   // stages are refilled from there until k-step 1 of the next slab.
   constexpr int M = TM * TN, R1 = TM >= 4 ? 2 : 1, Q1st = R1 * TN;
-  constexpr int kWait = (SA - 2) * IA + (SB - 2) * IB;   // loads that may still be in flight there
+  constexpr int kWait = kOne ? 0 : (SA - 2) * IA + (SB - 2) * IB;   // loads that may still be in flight there
   constexpr int E = SA > SB ? IB : SA < SB ? IA : (NV + 1) / 2;   // loads of a refill beside k-step 1
   auto slab = [&](auto refill, int kt) {
 #pragma unroll
@@ -290,7 +300,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
       acc[i][j] = mfma16<DT>(bf[1][j], af[i], acc[i][j]);
       __builtin_amdgcn_sched_barrier(0);
       const int p = q - (Q1st - 1);
-      if (p == 0) {
+      if (p == 0 && !kOne) {
         wait_loads<kWait>();
         lds_barrier();
         fa = ca;
@@ -300,7 +310,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
         ca = ca + 1 == SA ? 0 : ca + 1;
         cb = cb + 1 == SB ? 0 : cb + 1;
       }
-      if (p >= 0) {   // past the last slab: zeros, or what the stage last held; never used
+      if (p >= 0 && !kOne) {   // past the last slab: zeros, or what the stage last held; never used
         if (p < R1) read_a(ca, 0, p);
         else if (j == TN - 1) read_a(ca, 0, i);
         if (p < TN) read_b(cb, 0, p);
@@ -312,7 +322,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
     }
   };
   slab(std::false_type{}, 0);   // the prologue filled every stage
-  for (int kt = 1; kt < nk; ++kt) slab(std::true_type{}, kt);
+  if constexpr (!kOne)
+    for (int kt = 1; kt < nk; ++kt) slab(std::true_type{}, kt);
   wait_loads<0>();   // no load into LDS outlives its stage
 
   // Epilogue: GELU on the binary32 accumulators, rounded to the 16-bit format,
@@ -348,7 +359,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_kernel(GemmArgs g) {
         if (row >= (uint32_t)g.m || col >= (uint32_t)g.n) continue;
         uint16_t* yr = g.y + (int64_t)row * g.ldy + col;
         if (col + 8 > (uint32_t)g.n) store_head(yr, g.n - col, v[q]);
-        else if (g.vec) __builtin_nontemporal_store(v[q], reinterpret_cast<u32x4*>(yr));
+        else if (g.nt) __builtin_nontemporal_store(v[q], reinterpret_cast<u32x4*>(yr));
         else *reinterpret_cast<u32x4_any*>(yr) = v[q];
       }
       __builtin_amdgcn_wave_barrier();
@@ -371,42 +382,63 @@ void launch_tile(GemmArgs g, hipStream_t s) {
                      dim3(64 * WM * WN), 0, s, g);
 }
 
-// The tiles, and what a launch of each takes (measured with the GELU in bf16, random
-// operands, every CU busy): `per_cu` workgroups fit a CU; a round of them takes
-// `fixed` + slab us per 64 elements of k, with `slab1` while there is no more than
-// one per CU, and every further round of tiles adds `again` + slab. Large tiles
-// need the least operand traffic, small ones fill the chip where m n is small;
-// the estimate picks between them. Over 70 random shapes (m to 16384, n to
-// 4096, k to 4096) the picks took 1.9 % longer than the best of sixteen
-// tiles measured on each. A launch takes fewer than 2^32 threads: a tile whose
-// grid has more is passed over (only past 2^30 rows; 128 x 128 and the larger
-// ones have 512 threads, the others 256).
+// The tiles, and what a launch of each takes, in us:
+//   first + s slab                  the first tile of the busiest CU (s slabs of 64 elements of k)
+//   + (c - 1) (next + s next_slab)  c = ceil(tiles / CUs): the other tiles of that CU
+//   + f (out + s load)              f = tiles / CUs: what all CUs share (L2 and memory);
+//                                   out + gelu with the GELU, load + split where a row's
+//                                   128 bytes of a slab lie on two lines
+// Large tiles need the least operand traffic, small ones fill the chip where
+// m n is small and overlap their first loads and their outputs where k is
+// short; the estimate picks between them. k of one slab takes the tiles with one
+// stage, longer k the others. Fitted to every tile's times on 1240 shapes (m to
+// 16384, n to 4096, k to 4096, rows of x, w and y aligned and not, operands warm
+// and cold; 300 shapes for one slab). On 880 others the picks took 0.4 % longer
+// than the best tile measured on each, and 1.83x less time than the kernel of
+// 128-wide tiles (2 of the 880 took over 5 % longer); the estimate before, of six
+// tiles, took 1.51x less, but up to twice as long where k has few slabs. Whether
+// the rows of y are aligned makes 0-4 % of difference and none to the pick. A
+// launch takes fewer than 2^32 threads: a tile whose grid has more is passed over
+// (only past 2^30 rows, where k of one slab takes the tiles for longer k).
 struct Tile {
-  int bm, bn, threads, per_cu;
-  float fixed, again, slab1, slab;
+  uint32_t bm, bn, threads;
+  float first, slab, next, next_slab, out, load, split, gelu;
 };
+constexpr int kFirstOne = 11;   // from here on one stage
 constexpr Tile kTiles[] = {
-    {256, 256, 512, 1, 13.0f, 8.3f, 1.30f, 1.30f},
-    {256, 192, 512, 1, 11.0f, 6.6f, 1.01f, 1.01f},
-    {128, 128, 512, 1, 5.9f, 4.1f, 0.44f, 0.44f},
-    {128, 64, 256, 2, 4.2f, 2.5f, 0.32f, 0.56f},
-    {64, 64, 256, 2, 3.7f, 1.5f, 0.19f, 0.37f},
-    {64, 32, 256, 1, 3.6f, 2.2f, 0.155f, 0.155f},
+    {256, 256, 512, 6.04f, 0.920f, 3.48f, 1.150f, 3.44f, 0.420f, 0.125f, 4.92f},
+    {256, 192, 512, 5.55f, 0.860f, 4.85f, 0.776f, 1.83f, 0.224f, 0.160f, 4.93f},
+    {128, 128, 512, 4.46f, 0.423f, 2.20f, 0.418f, 0.92f, 0.056f, 0.117f, 1.45f},
+    {128, 128, 512, 3.82f, 0.364f, 0.94f, 0.216f, 0.50f, 0.208f, 0.113f, 1.06f},
+    {128, 96, 256, 3.93f, 0.329f, 1.52f, 0.343f, 1.11f, 0.058f, 0.137f, 1.51f},
+    {128, 64, 512, 3.18f, 0.306f, 0.12f, 0.157f, 0.71f, 0.101f, 0.092f, 0.39f},
+    {128, 64, 256, 3.21f, 0.266f, 0.41f, 0.184f, 0.77f, 0.073f, 0.085f, 0.73f},
+    {64, 64, 256, 3.02f, 0.202f, 0.41f, 0.133f, 0.40f, 0.031f, 0.045f, 0.29f},
+    {64, 64, 256, 2.80f, 0.287f, 0.00f, 0.123f, 0.48f, 0.023f, 0.053f, 0.20f},
+    {64, 32, 256, 2.72f, 0.165f, 0.10f, 0.080f, 0.38f, 0.009f, 0.034f, 0.13f},
+    {64, 32, 256, 2.55f, 0.238f, 0.00f, 0.080f, 0.35f, 0.017f, 0.028f, 0.07f},
+    {128, 128, 512, 3.38f, 0.0f, 0.00f, 0.0f, 1.26f, 0.0f, 0.0f, 1.08f},
+    {64, 64, 256, 2.86f, 0.0f, 0.27f, 0.0f, 0.15f, 0.0f, 0.0f, 0.22f},
+    {64, 32, 256, 2.55f, 0.0f, 0.18f, 0.0f, 0.17f, 0.0f, 0.0f, 0.08f},
 };
+constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
 
-inline int pick_tile(int64_t m, int64_t n, int64_t k, int cus) {
+// m, n < 2^31. About 0.1 us (32-bit divisions; a call's own time counts in the
+// smallest products).
+inline int pick_tile(uint32_t m, uint32_t n, uint32_t k, bool split, bool gelu, int cus) {
   const double slabs = (double)((k + kBK - 1) / kBK);
+  auto grid = [&](const Tile& t) { return (uint64_t)((m - 1) / t.bm + 1) * ((n - 1) / t.bn + 1); };
+  auto fits = [](const Tile& t, uint64_t tiles) { return tiles * t.threads <= UINT32_MAX; };
+  const bool one = k <= kBK && fits(kTiles[kFirstOne], grid(kTiles[kFirstOne]));
   int best = 0;   // where no tile's grid can be launched: the launch reports it
   double best_us = -1;
-  for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+  for (int i = one ? kFirstOne : 0; i < (one ? kTileCount : kFirstOne); ++i) {
     const Tile& t = kTiles[i];
-    const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn);
-    if (tiles * t.threads > (int64_t)UINT32_MAX) continue;
-    const int64_t slots = (int64_t)t.per_cu * cus;
-    const int64_t full = tiles / slots, rest = tiles % slots;
-    const double rounds = (double)(full + (rest != 0));
-    const double us = t.fixed + (rounds - 1) * t.again + (double)full * slabs * t.slab +
-                      (rest == 0 ? 0.0 : slabs * (rest <= cus ? t.slab1 : t.slab));
+    const uint64_t tiles = grid(t);
+    if (!fits(t, tiles)) continue;
+    const double share = (double)tiles / cus, others = std::ceil(share) - 1;
+    const double us = t.first + slabs * t.slab + others * (t.next + slabs * t.next_slab) +
+                      share * (t.out + (gelu ? t.gelu : 0.0) + slabs * (t.load + (split ? t.split : 0.0)));
     if (best_us < 0 || us < best_us) {
       best = i;
       best_us = us;
@@ -421,9 +453,17 @@ void launch_gemm(int tile, const GemmArgs& g, hipStream_t s) {
     case 0: launch_tile<DT, 256, 256, 2, 4, 3, 2>(g, s); break;
     case 1: launch_tile<DT, 256, 192, 4, 2, 2, 3>(g, s); break;
     case 2: launch_tile<DT, 128, 128, 4, 2, 5, 5>(g, s); break;
-    case 3: launch_tile<DT, 128, 64, 2, 2, 3, 3>(g, s); break;
-    case 4: launch_tile<DT, 64, 64, 2, 2, 4, 4>(g, s); break;
-    default: launch_tile<DT, 64, 32, 2, 2, 8, 8>(g, s); break;
+    case 3: launch_tile<DT, 128, 128, 4, 2, 2, 3>(g, s); break;
+    case 4: launch_tile<DT, 128, 96, 2, 2, 3, 3>(g, s); break;
+    case 5: launch_tile<DT, 128, 64, 4, 2, 2, 2>(g, s); break;
+    case 6: launch_tile<DT, 128, 64, 2, 2, 3, 3>(g, s); break;
+    case 7: launch_tile<DT, 64, 64, 2, 2, 4, 4>(g, s); break;
+    case 8: launch_tile<DT, 64, 64, 2, 2, 2, 2>(g, s); break;
+    case 9: launch_tile<DT, 64, 32, 2, 2, 4, 4>(g, s); break;
+    case 10: launch_tile<DT, 64, 32, 2, 2, 2, 2>(g, s); break;
+    case 11: launch_tile<DT, 128, 128, 4, 2, 1, 1>(g, s); break;
+    case 12: launch_tile<DT, 64, 64, 2, 2, 1, 1>(g, s); break;
+    default: launch_tile<DT, 64, 32, 2, 2, 1, 1>(g, s); break;
   }
 }
 
@@ -450,12 +490,21 @@ extern "C" quake_status quake_linear_gelu(const void* x, const void* w, void* y,
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
-  const int tile = pick_tile(m, n, k, cus);
+  // a row's 128 bytes of a slab on two lines, for some rows
+  const bool split = ldx % kBK != 0 || ldw % kBK != 0 || ((uintptr_t)x | (uintptr_t)w) % kSlabRow != 0;
+  const int tile = pick_tile((uint32_t)m, (uint32_t)n, (uint32_t)k, split, gelu != 0, cus);
   const Affine af = gelu_affine(mode);
-  const bool vec = aligned16(y) && (ldy % 8 == 0 || m == 1);
+  // Non-temporal stores of y: whole aligned vectors of an output past 8 MB and
+  // more than one slab. Smaller outputs fit L2 and are up to 12 % faster without
+  // (2.6 MB, 743 x 1736 x 8: 3.9 against 4.3 us); with one slab nearly all of the
+  // time is the write, and an output past 64 MB is 1.4-1.6x faster without. Past
+  // 8 MB with more slabs 0-9 % slower without (14395 x 3872 x 240: 63.7 against
+  // 58.7 us). Unaligned rows: their vectors share lines with the next tile's, so
+  // that L2 has to merge them (8210 x 3081 x 16: 27.5 against 38.4 us).
+  const bool nt = aligned16(y) && (ldy % 8 == 0 || m == 1) && k > kBK && m * n >= int64_t(1) << 22;
   const GemmArgs g{static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w),
                    static_cast<uint16_t*>(y), (int32_t)m, (int32_t)n, (int32_t)k, ldx, ldw, ldy,
-                   af.c0, af.c1, gelu_a(), 0, 0, gelu ? (int32_t)mode : -1, (uint32_t)vec};
+                   af.c0, af.c1, gelu_a(), 0, 0, gelu ? (int32_t)mode : -1, (uint32_t)nt};
   const hipStream_t s = static_cast<hipStream_t>(stream);
   if (dtype == QUAKE_BF16)
     launch_gemm<BF16>(tile, g, s);

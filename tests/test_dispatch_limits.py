@@ -1,8 +1,12 @@
-"""The softmax kernels' row-length limits as the source defines them, checked
-against the limits the C header documents and the boundaries the GPU tests
-exercise (CPU only; reads the sources, runs nothing)."""
+"""The softmax kernels' row-length limits and the linear+GELU tiles as the
+source defines them, checked against the limits the C header documents and the
+boundaries and tiles the GPU tests exercise (CPU only; reads the sources, runs
+nothing)."""
 import os
 import re
+
+import gemm_tiles
+from test_gpu_linear import TILE_SHAPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = open(os.path.join(ROOT, "paper_2412_00408_amd", "csrc", "softmax.hip")).read()
@@ -55,3 +59,38 @@ def test_gpu_tests_cover_each_resident_shape_boundary():
 def test_split_chunk_is_the_documented_16384():
     assert _int(r"constexpr int64_t kChunkElems = (\d+);") == 16384
     assert "ceil(cols / 16384)" in HDR
+
+
+def test_gemm_table_and_launches_agree():
+    assert len(gemm_tiles.TILES) == len(gemm_tiles.LAUNCHES) == 14
+    for i, (row, (bm, bn, wm, wn, sa, sb)) in enumerate(zip(gemm_tiles.TILES, gemm_tiles.LAUNCHES)):
+        assert row[:3] == (bm, bn, 64 * wm * wn)
+        assert (i >= gemm_tiles.FIRST_ONE) == ((sa, sb) == (1, 1))
+        assert 128 * (sa * bm + sb * bn) <= 160 * 1024
+
+
+def test_gemm_one_slab_takes_one_stage_and_huge_grids_fit():
+    for m, n in ((1, 1), (37, 3072), (4096, 768), (16384, 4096), (2 ** 30, 8), (2 ** 31 - 200, 8),
+                 (2 ** 31 - 300, 128)):
+        for k in (8, 64, 72, 128, 4096):
+            i = gemm_tiles.pick(m, n, k)
+            bm, bn, threads = gemm_tiles.TILES[i][:3]
+            assert -(-m // int(bm)) * -(-n // int(bn)) * threads < 2 ** 32
+            assert (i >= gemm_tiles.FIRST_ONE) == (k <= 64 and m < 2 ** 30)
+
+
+def test_gpu_tests_cover_every_gemm_tile():
+    """Each tile with rows of y aligned and not, with at least as many slabs as
+    its stages, and (where some shape of the range is given fewer) with fewer."""
+    seen = {}
+    for m, n, k in TILE_SHAPES:
+        for gelu in (True, False):
+            i = gemm_tiles.pick(m, n, k, gelu)
+            few = gemm_tiles.slabs(k) < max(gemm_tiles.LAUNCHES[i][4:])
+            seen.setdefault(i, set()).update({n % 8 == 0, "few" if few else "more"})
+    for i, (bm, bn, wm, wn, sa, sb) in enumerate(gemm_tiles.LAUNCHES):
+        want = {True, False, "more"}
+        if (bm, bn, sa, sb) in ((256, 256, 3, 2), (256, 192, 2, 3), (128, 128, 2, 3), (64, 64, 4, 4),
+                                (64, 32, 4, 4)):
+            want.add("few")
+        assert want <= seen.get(i, set()), (i, (bm, bn, sa, sb), seen.get(i))

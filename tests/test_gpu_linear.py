@@ -104,13 +104,21 @@ def test_wide_tile_grid(q, m, n, k, mode, dt):
                "linear wide %s %dx%dx%d mode %d gelu %d" % (dt, m, n, k, mode, gelu), dt)
 
 
-# every tile the dispatch has, on 256 CUs (in the order of its table), with
-# ragged last rows and columns, fewer and more slabs than the tile has stages and
-# a k tail; rows of y 16-byte aligned (n a multiple of 8) and not. The bound is
-# the module's; the oracle sees sampled rows and every column of them.
+# Every tile the dispatch has, on 256 CUs, with ragged last rows and columns and a
+# k tail, rows of y 16-byte aligned (n a multiple of 8) and not; for tiles that
+# the rule also gives fewer slabs than they have stages, such a k too. Which tile
+# a shape takes is checked on the CPU (test_dispatch_limits.py). The bound is the
+# module's; the oracle sees sampled rows and every column of them.
 TILE_SHAPES = [(8190, 4090, 72), (4000, 4088, 1032), (4050, 3060, 1096), (4090, 3064, 200),
                (1000, 3000, 1000), (1030, 2050, 264), (2040, 1016, 1096), (300, 3072, 72),
-               (513, 1030, 8), (500, 512, 4096), (37, 3001, 776)]
+               (513, 1030, 8), (500, 512, 4096), (37, 3001, 776),
+               (13950, 987, 72), (13144, 936, 152), (12486, 928, 96), (16133, 570, 216),
+               (15928, 224, 1080), (16082, 229, 1072), (10701, 216, 72), (11743, 197, 72),
+               (15783, 136, 464), (13672, 139, 496), (11474, 280, 72), (10996, 277, 80),
+               (8200, 104, 264), (10790, 97, 264), (5533, 112, 152), (7023, 103, 144),
+               (4941, 97, 208), (11615, 168, 80), (11714, 169, 72), (77, 40, 136),
+               (67, 35, 264), (69, 40, 72), (70, 39, 72), (13791, 736, 8), (13692, 723, 16),
+               (12743, 104, 8), (8166, 117, 8), (69, 40, 8), (73, 38, 8)]
 
 
 @pytest.mark.parametrize("m,n,k", TILE_SHAPES)
@@ -194,6 +202,25 @@ def test_unaligned_rows_take_no_longer(q):
         say("linear unaligned rows", m, n, k, "%.2f us, aligned %.2f us" % tuple(us))
         ratio *= us[0] / us[1]
     assert ratio ** 0.2 < 1.18, ratio ** 0.2
+
+
+def test_few_slabs_cost_little_beside_the_output(q):
+    """Products of one to four slabs of k, whose time is mostly their output's,
+    against the elementwise GELU of that output (one read and one write of it).
+    The geometric mean of the six ratios was 1.93 with tiles that leave a CU to
+    one or two workgroups, and is 1.46 with tiles of one to three stages; the bound
+    is halfway, and runs differ by 2-4 %."""
+    ratio = 1.0
+    for m, n, k in ((6541, 2960, 64), (8540, 2376, 64), (3140, 3344, 56), (1645, 2824, 88),
+                    (7334, 584, 120), (2438, 3776, 64)):
+        x = torch.randn(m, k, device="cuda:0").bfloat16()
+        w = (torch.randn(n, k, device="cuda:0") / k ** 0.5).bfloat16()
+        y = torch.empty((m, n), dtype=x.dtype, device="cuda:0")
+        z = torch.empty_like(y)
+        us = [_graph_us(lambda: q.quake_linear_gelu(x, w, y=y)), _graph_us(lambda: q.quake_gelu(y, z))]
+        say("linear few slabs", m, n, k, "%.2f us, its output's GELU %.2f us" % tuple(us))
+        ratio *= us[0] / us[1]
+    assert ratio ** (1 / 6) < 1.68, ratio ** (1 / 6)
 
 
 def test_strided_rows(q):
