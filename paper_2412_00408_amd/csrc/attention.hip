@@ -703,24 +703,6 @@ __global__ __launch_bounds__(kAttnThreads, QG == 1 ? 3 : 2) void attn_long_kerne
 // rows past the folded clamp's range take the unpipelined code after the loop.
 constexpr int kPipeSlots = 4;   // 4 KB each per wave: pass 1 four K blocks, pass 2 two of K, two of V^T
 
-// 16 bytes per lane from base + off (base uniform, off per lane) to LDS bytes
-// lds + 16 * lane (lds uniform). The asm has no register result: the data is in
-// LDS once vmcnt says so. M0 is used by nothing else here.
-__device__ __forceinline__ void lds_load16(uint32_t lds, uint32_t off, const void* base) {
-  const uint64_t b = (uint64_t)base;   // uniform already; readfirstlane says so to the compiler
-  const uint64_t sbase = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
-                         (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(off), "s"(sbase)
-               : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
 template <int DT, int MODE, int VK>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_pipe_kernel(AttnArgs g) {
   constexpr int QG = 2, W = kAttnWaves;
@@ -775,13 +757,13 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_pipe_kernel(AttnArgs g) 
   const uint32_t voff = 2u * (uint32_t)(lane >> 2) * (uint32_t)g.ldv +
                         16u * ((lane & 3) ^ vswz(lane >> 2));
   auto load_k = [&](int i, int slot) {
-    const char* base = reinterpret_cast<const char*>(K + (int64_t)(W * i + wave) * 32 * kAttnD);
+    const char* base = scalar_base(K + (int64_t)(W * i + wave) * 32 * kAttnD);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       lds_load16(lds0 + 4096 * slot + 1024 * j, koff ^ (16 * (j & 1)), base + 1024 * j);
   };
   auto load_v = [&](int i, int slot) {
-    const char* base = reinterpret_cast<const char*>(Vt + (W * i + wave) * 32);
+    const char* base = scalar_base(Vt + (W * i + wave) * 32);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       lds_load16(lds0 + 4096 * slot + 1024 * j, voff, base + (int64_t)32 * g.ldv * j);

@@ -89,25 +89,9 @@ struct GemmArgs {
 // where lanes past the end of k load from
 __device__ const u32x4 g_zero16 = {0u, 0u, 0u, 0u};
 
-// 16 bytes per lane from each lane's p to LDS bytes lds + 16 * lane (lds
-// uniform). The asm has no register result: the data is in LDS once vmcnt says
-// so. (Issued through the builtin, every later LDS read would wait for every
-// such load, as the compiler does not tell the stages apart. M0 is used by
-// nothing else here.)
-__device__ __forceinline__ void lds_load16(uint32_t lds, const char* p) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds), "v"(p)
-               : "memory");
-}
-// at most N vector memory operations of this wave still in flight
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 // the workgroup's barrier, no LDS access of this wave outstanding or moved across
 __device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  wait_lds();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }

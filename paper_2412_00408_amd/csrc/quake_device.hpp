@@ -260,6 +260,52 @@ __device__ __forceinline__ void store1(void* p, int64_t i, float v) {
 }
 
 // ---------------------------------------------------------------------------
+// Loads from memory to LDS without registers: 16 bytes per lane to LDS bytes
+// lds + 16 * lane (lds uniform). Inline asm with no register result, the data
+// being in LDS once vmcnt says so: issued through the builtin, every later LDS
+// read would wait for every such load, as the compiler does not tell the stages
+// of a buffer apart. The compiler looks for neither M0 nor hazards inside, so the
+// asm names M0 as written and puts a wait state between that write and the load;
+// and a uniform base comes from scalar_base, below.
+// ---------------------------------------------------------------------------
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // M0 is reserved; naming it is what is wanted
+// from each lane's p
+__device__ __forceinline__ void lds_load16(uint32_t lds, const void* p) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(lds), "v"(p)
+               : "memory", "m0");
+}
+// from base + off (base from scalar_base, off per lane, below 2^31)
+__device__ __forceinline__ void lds_load16(uint32_t lds, uint32_t off, const char* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// p (uniform) as a scalar instruction wrote it: a memory instruction has to stand
+// five wait states after a VALU instruction (v_readfirstlane, say) that wrote the
+// scalar registers it reads, and none after a scalar one, as which additions to
+// the result are compiled too. Copying inside lds_load16 instead cost attention 0.8 %,
+// waiting there 2.3 %.
+__device__ __forceinline__ const char* scalar_base(const void* p) {
+  uint64_t b = (uint64_t)p;
+  b = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  asm volatile("s_mov_b64 %0, %0" : "+s"(b));
+  return (const char*)b;
+}
+// at most N vector memory operations of this wave still in flight
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// no LDS access of this wave outstanding or moved across
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// ---------------------------------------------------------------------------
 // 64-lane reductions. Four DPP steps make every lane of a 16-lane row hold the
 // row's result (xor 1, xor 2 via quad_perm; xor 4 via row_half_mirror; xor 8
 // via row_mirror); then row_bcast:15 combines rows 0 and 1 into row 1 and rows
