@@ -1094,7 +1094,8 @@ static CausalArg causal_at(const SmArgs& a, int64_t r0) {
                    (uint32_t)std::min<uint64_t>(inv, UINT32_MAX)};
 }
 
-constexpr int64_t kRowChunk = int64_t(1) << 28;   // rows per launch (grid stays < 2^31)
+// Workgroups of one launch: it takes fewer than 2^32 threads.
+constexpr int64_t max_grid(int block) { return UINT32_MAX / block; }
 
 template <int DT, int MODE, bool FUSE, bool CAUSAL, int NV, int WAVES>
 static quake_status launch_rows(const SmArgs& a) {
@@ -1102,6 +1103,7 @@ static quake_status launch_rows(const SmArgs& a) {
   constexpr int RPB = kSmBlock / (64 * WAVES);
   const uint32_t nvr = (uint32_t)(a.cols / V);
   const bool full = !CAUSAL && nvr == (uint32_t)(64 * WAVES * NV);
+  constexpr int64_t kRowChunk = RPB * max_grid(kSmBlock);   // rows per launch
   for (int64_t r0 = 0; r0 < a.rows; r0 += kRowChunk) {
     const int64_t nr = std::min(kRowChunk, a.rows - r0);
     const uint32_t grid = (uint32_t)((nr + RPB - 1) / RPB);
@@ -1139,8 +1141,7 @@ static quake_status launch_causal_pair(const SmArgs& a, int64_t* rows_done) {
   pa.J = pa.M / 2 + (pa.M & 1) + K;
   pa.write_masked = a.write_masked;
   const int64_t nblocks = a.rows / P;
-  // blocks per launch: keep the job count (and the grid) below 2^31
-  const int64_t per = std::max<int64_t>(1, (int64_t(1) << 30) / pa.J);
+  const int64_t per = std::max<int64_t>(1, max_grid(kSmBlock) * (kSmBlock / 64) / pa.J);   // blocks per launch
   for (int64_t b0 = 0; b0 < nblocks; b0 += per) {
     const int64_t nb = std::min(per, nblocks - b0);
     pa.jobs = (uint32_t)(nb * pa.J);
@@ -1187,7 +1188,7 @@ struct ResShape {
 template <int DT, int MODE, bool FUSE, bool CAUSAL>
 static quake_status launch_long(const SmArgs& a) {
   constexpr int V = kV<DT>;
-  constexpr int64_t kLongRows = int64_t(1) << 30;      // rows per launch (one workgroup each)
+  constexpr int64_t kLongRows = max_grid(kLongBlock);  // rows per launch (one workgroup each)
   typedef ResShape<DT> RS;
   const uint32_t nvr = (uint32_t)(a.cols / V);
   for (int64_t r0 = 0; r0 < a.rows; r0 += kLongRows) {
@@ -1285,6 +1286,7 @@ static bool shifted_fits(const void* x, const void* y, int64_t rows, int64_t col
 template <int DT, int MODE, bool CAUSAL, int NV, int WAVES>
 static quake_status launch_rows_shifted(const SmArgs& a) {
   constexpr int RPB = kSmBlock / (64 * WAVES);
+  constexpr int64_t kRowChunk = RPB * max_grid(kSmBlock);   // rows per launch
   for (int64_t r0 = 0; r0 < a.rows; r0 += kRowChunk) {
     const int64_t nr = std::min(kRowChunk, a.rows - r0);
     const uint32_t grid = (uint32_t)((nr + RPB - 1) / RPB);
@@ -1301,7 +1303,7 @@ static quake_status launch_rows_shifted(const SmArgs& a) {
 template <int DT, int MODE>
 static quake_status launch_res_shifted(const SmArgs& a) {
   constexpr int V = kV<DT>;
-  constexpr int64_t kResRows = int64_t(1) << 30;       // rows per launch (one workgroup each)
+  constexpr int64_t kResRows = max_grid(kResBlock);    // rows per launch (one workgroup each)
   typedef ResShape<DT> RS;
   const int64_t nvm = (a.cols + 2 * V - 2) / V;
   const uint32_t cols = (uint32_t)a.cols;

@@ -464,6 +464,26 @@ def test_period_remainder_by_multiplication():
     assert (m == n % p).all()
 
 
+def test_rows_past_one_launch(q):
+    """2^28 + 5 rows of 8 take several launches (fewer than 2^32 threads each): the
+    plain softmax, and the paired-row kernel on square causal blocks."""
+    rows, cols = 2 ** 28 + 5, 8
+    say("softmax rows past one launch", rows, cols)
+    x = torch.zeros((rows, cols), dtype=torch.bfloat16, device="cuda:0")
+    x[:, 0] = (torch.arange(rows, device="cuda:0") % 3).to(torch.bfloat16)
+    y = torch.empty_like(x)
+    q.quake_softmax(x, y, mode=2)
+    for r0 in (0, 2 ** 26 - 10, 2 ** 27 - 12, rows - 13):
+        g, xs = y[r0:r0 + 13].contiguous(), x[r0:r0 + 13].contiguous()
+        ref = oracle.softmax(host_bits(xs), "bf16", 2, t=1.0)
+        assert_parity(host_bits(g), ref, "bf16", "op", "rows past one launch %d" % r0)
+    x.zero_()
+    q.quake_softmax_causal(x, y, period=8, shift=0, mode=2)
+    for r0 in (0, 2 ** 26 - 16, 2 ** 27, rows - 13):
+        r = torch.arange(r0, r0 + 13, device="cuda:0")
+        assert torch.equal((y[r0:r0 + 13] != 0).sum(1), r % 8 + 1), r0
+
+
 # Square causal blocks (period = cols, shift = 0, at most 64 vectors per row)
 # take the paired-row kernel: two rows per wave, r and M - 1 - r. Shapes cover
 # K = 0 and K > 0 (P above 63 vectors), odd M, one-vector rows, a trailing
