@@ -134,11 +134,11 @@ struct CausalArg {
   uint32_t inv;            // floor(2^32 / period), at most 2^32 - 1
 };
 
-// n mod period. q = floor(n inv / 2^32) is at most 2 below floor(n / period):
-// inv > 2^32 / period - 1 (for period 1 too), so n inv / 2^32 > n / period - 1.
+// n mod period. q = floor(n inv / 2^32) is at most 1 below floor(n / period):
+// 2^32 / period - 1 <= inv <= 2^32 / period (for period 1 too) and n < 2^32, so
+// n / period - 1 < n inv / 2^32 <= n / period.
 __device__ __forceinline__ uint32_t mod_period(uint32_t n, const CausalArg& ca) {
-  uint32_t r = n - (uint32_t)(((uint64_t)n * ca.inv) >> 32) * ca.period;
-  r = r >= ca.period ? r - ca.period : r;
+  const uint32_t r = n - (uint32_t)(((uint64_t)n * ca.inv) >> 32) * ca.period;
   return r >= ca.period ? r - ca.period : r;
 }
 

@@ -449,19 +449,26 @@ def test_causal_groups_and_row_ends(q, cols, dt, write_masked):
         assert np.all(gm == 0.0) if write_masked else np.all((gm == 0.0) | (gm == 7.0))
 
 
-def test_period_remainder_by_multiplication():
-    """The causal kernels' row mod period: q = floor(n floor(2^32 / p) / 2^32) and
-    two conditional subtractions, against % over its whole range (n < 2^32)."""
-    r = np.random.default_rng(5)
-    p = np.r_[1, 2, 3, 7, 512, 1001, 2**16, 2**16 + 1, 2**30, 2**31 - 1,
-              r.integers(1, 2**31, 4000)].astype(np.uint64)
-    n = np.r_[0, 1, 2**31, 2**32 - 1, r.integers(0, 2**32, 400)].astype(np.uint64)[:, None]
-    n = np.concatenate([np.broadcast_to(n, (len(n), len(p))), p[None] - 1, p[None], 2 * p[None] - 1])
-    inv = np.minimum((1 << 32) // p, (1 << 32) - 1).astype(np.uint64)
-    m = n - ((n * inv) >> np.uint64(32)) * p
-    for _ in range(2):
-        m = np.where(m >= p, m - p, m)
-    assert (m == n % p).all()
+def test_period_remainder(q):
+    """The causal kernels take row mod period by a multiplication with floor(2^32 /
+    period) and one subtraction. Rows of 8 zeros, whose outputs are 1 / L in their
+    L live entries: with shift = -(r0 mod period), L runs from 0 to 8 over the rows
+    from r0 on unless a period ends there. Launches take 2^26 - 4 rows, and a later
+    launch's first row has a remainder of its own."""
+    rows, cols = 2 ** 28 + 70001, 8
+    say("softmax causal periods", rows, cols)
+    x = torch.zeros((rows, cols), dtype=torch.bfloat16, device="cuda:0")
+    y = torch.empty_like(x)
+    for p in (1, 2, 3, 7, 1001, 65537, 2 ** 27 + 1, 2 ** 28 - 1, 2 ** 28 + 5, 2 ** 31 - 1):
+        for r0 in sorted({0, p - 1, p, 2 * p - 1, 5 * p + 3, (2 ** 28 // p) * p, 2 ** 26 - 7,
+                          2 ** 28 - 25, rows - 9}):
+            if r0 >= rows:
+                continue
+            q.quake_softmax_causal(x, y, period=p, shift=-(r0 % p), mode=2)
+            r = torch.arange(max(0, r0 - 20), min(rows, r0 + 40), device="cuda:0")
+            want = ((r % p) - (r0 % p) + 1).clamp(0, cols)
+            got = (y[r[0]:r[-1] + 1] != 0).sum(1)
+            assert torch.equal(got, want), (p, r0, got.tolist(), want.tolist())
 
 
 def test_rows_past_one_launch(q):
