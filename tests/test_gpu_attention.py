@@ -257,8 +257,9 @@ def _pipelined_heads(seq, causal):
 # the pipelined kernel against the one-group kernel on the same heads, bit for
 # bit: every count of key blocks mod 4 (its waves take 8 to 17 blocks), whole and
 # ragged last blocks and query groups, padded rows of V^T with NaN past the
-# keys, and scores past the folded clamp's range (scale 1e5: |c1| > 2^54), where
-# it takes the unpipelined code for every block
+# keys, and all scores past the folded clamp's range (scale 1e5: |c1| > 2^54),
+# where it takes the unpipelined code for every block and most rows are zero or
+# NaN (finite rows on that code: the test after this one)
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("seq,ldv,dt,mode,scale", [
     (1032, 1032, "bf16", 2, 1.0), (1056, 1056, "f16", 2, 1.0), (1088, 1088, "bf16", 0, 1.0),
@@ -277,6 +278,34 @@ def test_pipelined_and_one_group_give_the_same_bits(q, causal, seq, ldv, dt, mod
         one = q.quake_attention(qg[hd:hd + 1].contiguous(), kg[hd:hd + 1].contiguous(),
                                 vtg[hd:hd + 1].contiguous()[:, :, :seq], mode=mode, t=T, causal=causal)
         assert torch.equal(one[0].view(torch.int16), whole[hd].view(torch.int16)), hd
+
+
+# One query per tile of 64 scaled past the folded clamp's range (m t about 1e10,
+# |c1| > 2^54) takes the whole tile to the unpipelined code: the other 63 queries
+# there are finite, have the bits that they have with that query in range (where
+# their tile is pipelined), and one head of them is held to the oracle's bound
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("seq,ldv,mode", [(1056, 1056, 2), (1100, 1104, 1), (1208, 1208, 3),
+                                          (2056, 2064, 2)])
+def test_tiles_past_the_folded_clamp(q, causal, seq, ldv, mode):
+    heads = _pipelined_heads(seq, causal)
+    say("attention tiles past the folded clamp", heads, seq, ldv, mode, causal)
+    qc, kc, vtc = synth.attention_inputs(heads, seq, 150 + seq % 7, ldv=ldv, pad=float("nan"))
+    far = torch.arange(17, seq, 128)          # every other tile
+    qf = qc.clone()
+    qf[:, far] *= 2.0 ** 36                   # scores of about 2^36 N(0, 8^2): c0 m past 2^54
+    kg, vtg = kc.to("cuda:0"), vtc.to("cuda:0")
+    out, base = (q.quake_attention(a.to("cuda:0"), kg, vtg[:, :, :seq], mode=mode, t=T, causal=causal)
+                 for a in (qf, qc))
+    near = torch.ones(seq, dtype=torch.bool)
+    near[far] = False
+    near = near.to("cuda:0")
+    assert not torch.isnan(out[:, near]).any()
+    assert torch.equal(out[:, near].view(torch.int16), base[:, near].view(torch.int16))
+    hd = slice(heads // 2, heads // 2 + 1)
+    ins = tuple(host_bits(a[hd].contiguous()) for a in (qc, kc, vtc))
+    ref = oracle.attention(*ins, mode, T, causal)
+    _check(host_bits(base[hd].contiguous()), ref, ins, seq, causal, "tiles past the clamp s%d" % seq)
 
 
 @pytest.mark.parametrize("seq,ldv", [(777, 781), (777, 784), (1111, 1115), (2100, 2103),
