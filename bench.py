@@ -591,7 +591,8 @@ def linear_down(q, timer, synth, a):
     """The down-projection of the same BERT-base MLP, x [4096, 3072] times
     w [768, 3072]^T in bf16, the product alone (no activation follows it in
     the model): few output columns and a long k, where quake_linear_gelu
-    takes 192 tiles of 128 x 128. torch.matmul (the vendor BLAS) on the same operands for context.
+    takes 256 tiles of 128 x 96. torch.matmul (the vendor BLAS) on the same
+    operands for context.
     Eight rotating operand sets (about 290 MB)."""
     import torch
     m, n, k = 4096, 768, 3072

@@ -693,11 +693,13 @@ __global__ __launch_bounds__(kAttnThreads, QG == 1 ? 3 : 2) void attn_long_kerne
 //    blocks (one of S = K Q^T for the next block, one of O = V^T P for the
 //    probabilities finished in the chunks before) are issued, then the 30 VALU
 //    instructions of four QuAKE2 exponentials run beside them.
-// Pass 2 then issues VALU in all but 3 % of its cycles (2400 clocks per block of two groups
-// and wave with two waves per SIMD, 276 VALU instructions each); what is left is
-// power: the clock falls to 1.6-1.8 GHz. Measured against attn_long_kernel (us,
-// QuAKE2, same bits): 32 x 2048 76.4 -> 67.1 without the mask, 47.0 -> 41.3 with
-// it, 8 x 8192 276.6 -> 238.7 and 153.1 -> 130.1, 16 x 4001 with it 92.6 -> 70.0.
+// By counters (32 x 2048 without the mask, QuAKE2, attn_long_kernel -> this one):
+// VALU instructions per score 11.7 -> 10.7, a CU busy for 177 -> 139 thousand
+// clocks, VALU issue 0.55 -> 0.65 of them (at four clocks an instruction) and the
+// matrix cores 0.28 -> 0.36; busy clocks over time put the clock at 1.9 GHz. Graph
+// replays on one set of operands (us, QuAKE2, bf16, one machine in turn, same
+// bits): 32 x 2048 79.6 -> 70.1 without the mask, 49.1 -> 42.5 with it, 8 x 8192
+// 290.9 -> 250.9 and 160.4 -> 137.2, 16 x 4001 with it 97.2 -> 73.4.
 // Blocks that some group masks or skips (at most a wave's last: the two
 // diagonal blocks of a tile and the block past s are its last two) and
 // rows past the folded clamp's range take the unpipelined code after the loop.

@@ -274,10 +274,11 @@ __global__ __launch_bounds__(kSmBlock) void sm_rows_kernel(const char* __restric
   // live entries (uniform) is neither computed nor summed (every term would be
   // +0: the same bits), and only the vectors at the ends of the live range are
   // masked element by element. About half of the groups of a causal block go.
-  // bf16 96096 x 1001 (period 1001) was bound by VALU issue (98 % of its
-  // cycles): 58.1 -> 54.0 us with these, the uniform row and the row ends stored
-  // in at most three pieces (288 MB, 5.3 TB/s; the folded clamp and a cheaper
-  // boundary mask on top of it gave nothing more).
+  // bf16 96096 x 1001 (period 1001) issued 400 VALU instructions per row and
+  // waited to issue for 0.32 of its waves' time; with these, the uniform row and
+  // the row ends stored in at most three pieces 248 and 0.18, 58.1 -> 54.0 us
+  // (288 MB, 5.3 TB/s; the folded clamp and a cheaper boundary mask on top of it
+  // gave nothing more).
   // Not for rows that their memory time bounds (binary32, and aligned rows of a
   // workgroup, below 8 groups): 2 % slower there.
   constexpr bool kSkip = CAUSAL && (NV >= 8 || (DT != F32 && (WAVES == 1 || SHIFT)));
